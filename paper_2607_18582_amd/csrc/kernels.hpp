@@ -289,7 +289,64 @@ struct CowArgs {                           // one copy-on-write parameter copy
 
 struct DevRecord { int op, neuron, partner, pad; int64_t noise_off, scratch_off; };
 
+// ---- image-resident chains (k_chain.hip; planned by chain.cpp)
+// A node's activation in a block's LDS: image i's pixel (y, x), channel byte
+// c2, is at i * arena + off + p * pxb + (c2 ^ swizzle(p)) with
+// p = (y + bd) * pitch + x + bd and swizzle(p) = ((p >> sh) & mask) << 4.
+// bd = 1: a border of zeros around the image (read by 3 x 3 filters).  pxb
+// and the swizzle spread the 16-byte slots that a half wave reads together
+// over the LDS banks.
+struct ChainT {
+  int off = 0, pitch = 0, pxb = 0, bd = 0, sh = 0, mask = 0;
+};
+
+enum { CH_LOAD = 0, CH_STORE = 1, CH_CONV = 2, CH_DW = 3, CH_ADD = 4, CH_GAP = 5 };
+
+struct ChainOp {
+  int kind = 0, code = 0;                // code: convolution instance
+  ChainT in, skip, out;
+  int H = 0, W = 0, C = 0;               // input geometry (LOAD, STORE, ADD, GAP: the tensor's)
+  int Ho = 0, Wo = 0, Cout = 0, K = 0, stride = 1, relu = 0;
+  int lw = 0, lp = 0;                    // log2 of Wo and of Ho * Wo
+  int n0 = 0, oc = 0;                    // a slice of output channels: first weight row, first
+                                         // channel in out
+  int add = 0, add_relu = 0, cpad = 0, Cs = 0;   // ADD (1 identity, 2 option A) of skip
+  int same = 0;                          // ... which stands where out does
+  int zero = 0;                          // out has a border to clear
+  int groups = 1, splits = 1, inv = 256; // conv16: groups of channel tiles, parts of the pixel
+                                         // tiles, and (w inv) >> 8 = w / groups for w < CHAIN_WAVES
+  int node = 0, w = 0, b = 0;            // weighted ops: node, offsets into the pointer tables
+  int wbytes = 0, woff = 0;              // ... bytes of its weights (0: none) and where they start
+  int buf = 0;                           // LOAD, STORE, GAP: launch buffer
+  DivU32 dcv;                            // divider by C / 8 (DW: by C / 4; CONV: unused)
+};
+
+struct ChainBuf {
+  void* p = nullptr;
+  int mode = MODE_BUF;
+  int64_t row_elems = 0;
+};
+constexpr int CHAIN_BUFS = 24;
+
+struct ChainArgs {
+  const ChainOp* ops = nullptr;          // device
+  int nops = 0;
+  const void* const* tabs = nullptr;     // pointer tables, offset to the launch's first slot
+  int nslots = 0, nx = 0, x0 = 0;
+  int G = 1, arena = 0;                  // images per block, LDS bytes per image
+  int per_slot = 0, turns = 0;           // filled by the launcher: blocks per slot, blocks per XCD
+  VirtualIn vin;                         // buffer 0 read through channel maps (vin.chmap set)
+  ChainBuf buf[CHAIN_BUFS];
+};
+constexpr int CHAIN_LDS = 160 * 1024 / 2;   // two blocks per CU
+constexpr int CHAIN_OPS = 48;               // most operations
+constexpr int CHAIN_LIST = 64;              // changed channels of a virtual input listed in LDS
+// LDS past the arenas: a zero slot, an unread slot, pointers, the list
+constexpr int CHAIN_EXTRA = 32 + 16 * CHAIN_OPS + 4 * (1 + 2 * CHAIN_LIST) + 12;
+constexpr int CHAIN_WAVES = 8;
+
 // launchers (return the launch status)
+hipError_t launch_chain(const ChainArgs& a, hipStream_t s);
 hipError_t launch_conv(const ConvArgs& a, int nslots, int dtype, hipStream_t s);
 hipError_t launch_conv_lds(const ConvArgs& a, int nslots, hipStream_t s);
 hipError_t launch_conv_big(const ConvArgs& a, int nslots, hipStream_t s);

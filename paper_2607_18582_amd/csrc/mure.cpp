@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "../../include/mure.h"
+#include "chain.hpp"
 #include "kernels.hpp"
 #include "plan.hpp"
 
@@ -85,13 +86,23 @@ struct Placement {
 };
 
 Placement place_buffers(const Graph& g, const std::vector<int>& nodes, const std::set<int>& external,
-                        const std::map<int, int>& fused = {}) {
+                        const std::map<int, int>& fused = {},
+                        const std::map<int, std::pair<ChainSeg, int64_t>>& chains = {}) {
   // nodes: executed in this order; external: nodes whose output lives
   // elsewhere; fused: conv_b -> ADD pairs run as one launch at conv_b's step,
-  // so the ADD's buffer is placed at that step (conv_b itself has none)
+  // so the ADD's buffer is placed at that step (conv_b itself has none);
+  // chains: runs of nodes executed as one launch, whose other outputs are
+  // never stored and whose inputs are in use until it ends
   std::map<int, int> last_use;
   for (int v : nodes) {
     for (int k = 0; k < g.nodes[v].n_in; ++k) last_use[g.nodes[v].in[k]] = v;
+  }
+  std::set<int> inside;
+  for (const auto& c : chains) {
+    const ChainSeg& s = c.second.first;
+    for (int p : s.ins) last_use[p] = std::max(last_use[p], s.b);
+    for (int v = s.a; v <= s.b; ++v)
+      if (std::find(s.outs.begin(), s.outs.end(), v) == s.outs.end()) inside.insert(v);
   }
   struct Blk { int64_t off, size; int owner; };
   std::vector<Blk> blocks;
@@ -115,6 +126,7 @@ Placement place_buffers(const Graph& g, const std::vector<int>& nodes, const std
     placed.insert(v);
   };
   for (int v : nodes) {
+    if (inside.count(v)) continue;
     // free blocks whose owner is no longer needed by v or later nodes
     for (Blk& b : blocks) {
       if (b.owner < 0) continue;
@@ -127,7 +139,7 @@ Placement place_buffers(const Graph& g, const std::vector<int>& nodes, const std
       if (!external.count(f->second)) place(f->second);
       continue;
     }
-    if (external.count(v) || placed.count(v)) continue;
+    if (external.count(v) || placed.count(v) || inside.count(v)) continue;
     place(v);
   }
   return pl;
@@ -158,6 +170,9 @@ struct mure_ctx {
   int32_t* slotv = nullptr;
   int32_t* chmapv = nullptr;
   DeltaCol* colv = nullptr;
+  ChainOp* chainv = nullptr;
+  std::vector<ChainSeg> chains;                       // plan_chains of the loaded model
+  std::map<int, std::pair<ChainSeg, int64_t>> orig_chains;   // run_original's (cached nodes stored)
   struct GroupTabs {
     std::map<int, int64_t> w, b;                      // node -> offset (in pointers) into tables
     int64_t slot_mutant = 0;                          // offset (int32) into slotv
@@ -172,6 +187,10 @@ struct mure_ctx {
     int64_t vgent = 0;                                // vhalo: offset (int32) into chmapv of the
                                                       // (slot, group) entries, one per side plane
     std::vector<int64_t> vgbeg;                       // vhalo: first entry of each slot (+1)
+    std::map<int, std::pair<ChainSeg, int64_t>> chains;   // chains of the suffix by first node, and
+                                                      // their first op (in chainv)
+    bool vchain = false;                              // the first chain reads mmi's output through
+                                                      // channel maps and is its only reader
   };
   std::vector<GroupTabs> gtabs;
   std::map<int, int64_t> orig_w, orig_b;              // node -> offset of 1-entry original tables
@@ -469,6 +488,85 @@ mure_status exec_node(mure_ctx* ctx, int v, const std::vector<Where>& ins, void*
   return MURE_OK;
 }
 
+// Whether the first chain of group gr's suffix can read mmi's output from the
+// prefix cache, the mutants' channel maps and compact delta rows: it starts
+// right after mmi and is its only reader.
+bool chain_reads_mmi(const std::vector<ChainSeg>& chains, const Graph& g, const Group& gr) {
+  if (gr.mmi >= g.out() || !(gr.delta || gr.n_recompute == 0)) return false;
+  const ChainSeg& s = chains[gr.mmi + 1];
+  if (!s.valid() || s.ins.empty() || s.ins[0] != gr.mmi) return false;
+  for (int v = s.b + 1; v <= g.out(); ++v)
+    for (int k = 0; k < g.nodes[v].n_in; ++k)
+      if (g.nodes[v].in[k] == gr.mmi) return false;
+  return true;
+}
+
+// Launch a chain over slots [0, nslots) of a chunk of nx inputs from x0 on;
+// `where` gives the buffers of its inputs and stored outputs, vin (optional)
+// the view of its first input.
+template <typename F>
+mure_status exec_chain(mure_ctx* ctx, const std::pair<ChainSeg, int64_t>& c, F&& where, const VirtualIn* vin,
+                       int cs0, int nslots, int nx, int x0, bool timed) {
+  const Graph& g = ctx->g;
+  const ChainSeg& s = c.first;
+  ChainArgs a;
+  a.ops = ctx->chainv + c.second;
+  a.nops = (int)s.ops.size();
+  a.tabs = ctx->tables + cs0;
+  a.nslots = nslots; a.nx = nx; a.x0 = x0;
+  a.arena = s.arena;
+  // fewer images per block while the launch would leave the chip idle
+  a.G = s.gmax;
+  while (a.G > 1 && (int64_t)((nx + a.G - 1) / a.G) * nslots < 1024) --a.G;
+  if (vin) a.vin = *vin;
+  int nb = 0;
+  double bytes = 0;
+  const int64_t es = 2;
+  for (const std::vector<int>* l : {&s.ins, &s.outs})
+    for (int v : *l) {
+      const Where w = where(v);
+      const int64_t row = g.nodes[v].out_elems();
+      a.buf[nb].p = const_cast<void*>(w.p);
+      a.buf[nb].mode = w.mode;
+      a.buf[nb].row_elems = row;
+      bytes += (double)(w.mode == MODE_CACHE ? nx : (int64_t)nx * nslots) * row * es;
+      ++nb;
+    }
+  timed = timed && ctx->kernel_timing;
+  if (timed) {
+    mure_status st = timing_begin(ctx);
+    if (st != MURE_OK) return st;
+  }
+  hipError_t e = launch_chain(a, ctx->stream);
+  if (e != hipSuccess) return ctx->dev_fail(e, "kernel launch");
+  ctx->stats.launches++;
+  if (timed) {
+    hipError_t ee = hipEventRecord(ctx->tevents[ctx->tevents_used + 1], ctx->stream);
+    if (ee != hipSuccess) return ctx->dev_fail(ee, "hipEventRecord");
+    ctx->tevents_used += 2;
+    // counted with the family that does most of its multiply-accumulates
+    int64_t macs = 0, by_fam[N_FAMILIES] = {};
+    for (int v = s.a; v <= s.b; ++v) {
+      const Node& n = g.nodes[v];
+      if (!n.weighted()) continue;
+      macs += n.macs;
+      by_fam[node_family(g, v)] += n.macs;
+      bytes += (double)nslots * n.n_weights() * es;
+    }
+    const int fam = (int)(std::max_element(by_fam, by_fam + N_FAMILIES) - by_fam);
+    const int64_t total = macs * nx * nslots;
+    ctx->tevent_family.push_back(fam);
+    ctx->tevent_mmi.push_back(0);
+    ctx->stats.gemm_launches++;
+    ctx->stats.gemm_macs_algorithmic += total;
+    ctx->stats.gemm_macs_executed += total;
+    ctx->stats.kernel_launches[fam]++;
+    ctx->stats.kernel_macs_algorithmic[fam] += total;
+    ctx->stats.kernel_bytes_algorithmic[fam] += bytes;
+  }
+  return MURE_OK;
+}
+
 // Invalidate the prefix cache; its device buffers stay allocated for reuse.
 void reset_cache(mure_ctx* ctx) { ctx->N = 0; }
 
@@ -630,6 +728,7 @@ static mure_status load_model_impl(mure_ctx* ctx, const mure_layer* layers, int3
     HIPTRY(hipStreamSynchronize(ctx->stream));
   }
   ctx->g = std::move(g);
+  ctx->chains = plan_chains(ctx->g);
   ctx->have_graph = true;
   ctx->plan = Plan();
   ctx->recs.clear();
@@ -794,9 +893,26 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
       ow[v] = (int64_t)tabs.size(); tabs.push_back(ctx->d_w[v]->p);
       ob[v] = (int64_t)tabs.size(); tabs.push_back(ctx->d_b[v]->p);
     }
+    std::vector<ChainOp> chops;
+    // the chain's operations with their pointer-table offsets
+    auto add_chain = [&](const ChainSeg& seg, const std::map<int, int64_t>& w, const std::map<int, int64_t>& b,
+                         std::map<int, std::pair<ChainSeg, int64_t>>& to) {
+      std::pair<ChainSeg, int64_t>& c = to[seg.a];
+      c.first = seg;
+      c.second = (int64_t)chops.size();
+      for (ChainOp o : seg.ops) {
+        if (o.wbytes > 0) {
+          o.w = (int)w.at(o.node);
+          o.b = (int)b.at(o.node);
+        }
+        chops.push_back(o);
+      }
+    };
     for (size_t gi = 0; gi < plan.groups.size(); ++gi) {
-      const Group& gr = plan.groups[gi];
+      Group& gr = plan.groups[gi];
       mure_ctx::GroupTabs& gt = gtabs[gi];
+      gt.vchain = chain_reads_mmi(ctx->chains, g, gr);
+      if (gt.vchain) virtual_map(g, plan, gr);
       for (int v = gr.mmi; v < (int)g.nodes.size(); ++v) {
         if (!g.nodes[v].weighted()) continue;
         gt.w[v] = (int64_t)tabs.size();
@@ -809,6 +925,15 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
           auto it = cow_index.find({mu, v});
           tabs.push_back(it == cow_index.end() ? ctx->d_b[v]->p : (const void*)cargs[it->second].b_dst);
         }
+      }
+      for (int v = gr.mmi + 1; v < (int)g.nodes.size(); ++v) {
+        const ChainSeg& seg = ctx->chains[v];
+        if (!seg.valid()) continue;
+        // mmi's output is not materialised for readers through maps or groups
+        const bool reads = std::find(seg.ins.begin(), seg.ins.end(), gr.mmi) != seg.ins.end();
+        if (reads && (gr.virt || gr.vhalo) && !gt.vchain) continue;
+        add_chain(seg, gt.w, gt.b, gt.chains);
+        v = seg.b;
       }
       gt.slot_mutant = (int64_t)slots.size();
       for (int mu : gr.mutants) slots.push_back(mu);
@@ -841,6 +966,16 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
         chmaps.insert(chmaps.end(), src.begin(), src.end());
         gt.vgent = (int64_t)chmaps.size();
         chmaps.insert(chmaps.end(), ent.begin(), ent.end());
+      }
+    }
+    std::map<int, std::pair<ChainSeg, int64_t>> ochains;
+    {
+      const std::set<int> keep(plan.cache_nodes.begin(), plan.cache_nodes.end());
+      for (int v = 1; v < (int)g.nodes.size(); ++v) {
+        ChainSeg seg;
+        if (!ctx->chains[v].valid() || !build_chain(g, v, ctx->chains[v].b, keep, seg)) continue;
+        add_chain(seg, ow, ob, ochains);
+        v = seg.b;
       }
     }
     // touched-channel lists of the recompute mutants (CSR, absolute offsets
@@ -891,6 +1026,7 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
     const size_t o_cols = section(cols.size() * sizeof(DeltaCol));
     const size_t o_cargs = section(cargs.size() * sizeof(CowArgs));
     const size_t o_drecs = section(drecs.size() * sizeof(DevRecord));
+    const size_t o_chops = section(chops.size() * sizeof(ChainOp));
     const size_t o_noise = section((size_t)pool_n * 4);
     HIPTRY(ctx->h_apply.ensure(std::max<size_t>(total, 256)));
     HIPTRY(ctx->d_apply.ensure(std::max<size_t>(total, 256)));
@@ -904,6 +1040,7 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
     put(o_cols, cols.data(), cols.size() * sizeof(DeltaCol));
     put(o_cargs, cargs.data(), cargs.size() * sizeof(CowArgs));
     put(o_drecs, drecs.data(), drecs.size() * sizeof(DevRecord));
+    put(o_chops, chops.data(), chops.size() * sizeof(ChainOp));
     fill_pool(reinterpret_cast<float*>(h + o_noise), segs, pool_n);
     hipStream_t st = ctx->stream;
     char* d = ctx->d_apply.as<char>();
@@ -912,6 +1049,7 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
     ctx->slotv = reinterpret_cast<int32_t*>(d + o_slots);
     ctx->chmapv = reinterpret_cast<int32_t*>(d + o_chmap);
     ctx->colv = reinterpret_cast<DeltaCol*>(d + o_cols);
+    ctx->chainv = reinterpret_cast<ChainOp*>(d + o_chops);
     if (!cargs.empty())
       HIPTRY(launch_cow(reinterpret_cast<const CowArgs*>(d + o_cargs), (int)cargs.size(),
                         reinterpret_cast<const DevRecord*>(d + o_drecs), reinterpret_cast<const float*>(d + o_noise),
@@ -922,6 +1060,7 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
     (void)hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1);
     ctx->stats.ms_apply = ms;
     ctx->gtabs = std::move(gtabs);
+    ctx->orig_chains = std::move(ochains);
     ctx->orig_w = std::move(ow);
     ctx->orig_b = std::move(ob);
   }
@@ -993,7 +1132,9 @@ static mure_status run_original_impl(mure_ctx* ctx, const void* inputs_dev, int6
     const int fa = ctx->fused ? fused_add_of(g, v) : -1;
     if (fa >= 0 && !cached.count(v)) fused[v] = fa;
   }
-  Placement pl = place_buffers(g, nodes, external, fused);
+  static const std::map<int, std::pair<ChainSeg, int64_t>> no_chains;
+  const auto& chains = ctx->fused ? ctx->orig_chains : no_chains;
+  Placement pl = place_buffers(g, nodes, external, fused, chains);
   const int64_t budget = ctx->max_ws_mb << 20;
   int64_t nx = n;
   if (ctx->chunk_inputs) nx = std::min<int64_t>(nx, ctx->chunk_inputs);
@@ -1021,6 +1162,13 @@ static mure_status run_original_impl(mure_ctx* ctx, const void* inputs_dev, int6
     std::set<int> done;
     for (int v = 1; v <= L; ++v) {
       if (done.count(v)) continue;
+      const auto ch = chains.find(v);
+      if (ch != chains.end()) {
+        mure_status st = exec_chain(ctx, ch->second, where, nullptr, 0, 1, cnt, (int)x0, false);
+        if (st != MURE_OK) return st;
+        v = ch->second.first.b;
+        continue;
+      }
       const Node& nd = g.nodes[v];
       std::vector<Where> ins;
       for (int k = 0; k < nd.n_in; ++k) ins.push_back(where(nd.in[k]));
@@ -1080,7 +1228,8 @@ struct ChunkGeom {
   int64_t nx = 0, spc = 0, cap_rows = 0, need_bytes = 0;
 };
 
-ChunkGeom group_geometry(const mure_ctx* ctx, int gi, int nslots, int64_t budget) {
+// chains: with the cluster's chains (whose inner nodes take no buffers).
+ChunkGeom group_geometry(const mure_ctx* ctx, int gi, int nslots, int64_t budget, bool chains) {
   const Graph& g = ctx->g;
   const Group& gr = ctx->plan.groups[gi];
   const int L = g.out(), mmi = gr.mmi;
@@ -1092,7 +1241,8 @@ ChunkGeom group_geometry(const mure_ctx* ctx, int gi, int nslots, int64_t budget
     const int fa = ctx->fused ? fused_add_of(g, v) : -1;
     if (fa >= 0) cg.fused_adds[v] = fa;
   }
-  cg.pl = place_buffers(g, nodes, {}, cg.fused_adds);
+  if (chains) cg.pl = place_buffers(g, nodes, {}, cg.fused_adds, ctx->gtabs[gi].chains);
+  else cg.pl = place_buffers(g, nodes, {}, cg.fused_adds);
   const int64_t peak = std::max<int64_t>(cg.pl.peak, 1);
   int64_t nx = N;
   if (ctx->chunk_inputs) nx = std::min<int64_t>(nx, ctx->chunk_inputs);
@@ -1122,7 +1272,14 @@ static mure_status run_group(mure_ctx* ctx, int gi, int s_begin, int s_end, uint
   const int64_t N = ctx->N;
   int64_t budget = ctx->max_ws_mb << 20;
   if (ws) budget = std::min(budget, ws_bytes);
-  const ChunkGeom cg = group_geometry(ctx, gi, s_end - s_begin, budget);
+  // a scratch array that holds the layer-by-layer chunk and not the chains'
+  // (whose inputs and outputs live at the same time) runs layer by layer
+  bool chains = ctx->fused != 0;
+  ChunkGeom cg = group_geometry(ctx, gi, s_end - s_begin, budget, chains);
+  if (ws && chains && cg.need_bytes > ws_bytes) {
+    chains = false;
+    cg = group_geometry(ctx, gi, s_end - s_begin, budget, false);
+  }
   const Placement& pl = cg.pl;
   const std::map<int, int>& fused_adds = cg.fused_adds;
   const int64_t nx = cg.nx, spc = cg.spc, cap_rows = cg.cap_rows;
@@ -1130,7 +1287,8 @@ static mure_status run_group(mure_ctx* ctx, int gi, int s_begin, int s_end, uint
   // caller's scratch array: the side planes live in a buffer of their own)
   const Node& nmm = g.nodes[mmi];
   const int64_t vP = (int64_t)nmm.H * nmm.W;
-  const bool vh = gr.vhalo && ctx->group_reads && ctx->fused && !ws && nx * vP < INT32_MAX;
+  const bool vc = gt.vchain && chains;             // mmi's output read by a chain, through maps
+  const bool vh = gr.vhalo && !vc && ctx->group_reads && ctx->fused && !ws && nx * vP < INT32_MAX;
   if (vh) {
     int64_t most = 0;
     for (int cs0 = s_begin; cs0 < s_end; cs0 += (int)spc) {
@@ -1183,7 +1341,7 @@ static mure_status run_group(mure_ctx* ctx, int gi, int s_begin, int s_end, uint
         for (int k = 0; k < nm.n_in; ++k) ins.push_back(where(nm.in[k]));
         void* out = const_cast<void*>(where(mmi).p);
         const int rec_end = std::min(cs1, gr.n_recompute);
-        const int pa = (gr.virt || vh) ? cs1 : gr.delta ? cs0 : std::max(cs0, gr.n_recompute);
+        const int pa = (gr.virt || vh || vc) ? cs1 : gr.delta ? cs0 : std::max(cs0, gr.n_recompute);
         if (pa < cs1) {
           PatchArgs a;
           a.cache = mmi_cache;
@@ -1207,7 +1365,7 @@ static mure_status run_group(mure_ctx* ctx, int gi, int s_begin, int s_end, uint
           ex.at_mmi = true;
           int launch_slots = rec_end - cs0;
           if (gr.delta) {
-            if (gr.virt || vh) ex.delta_T = gr.T;
+            if (gr.virt || vh || vc) ex.delta_T = gr.T;
             ex.exec_macs = tl * per_ch * cnt;
             ex.delta_channels = tl;
             if (node_family(g, mmi) == FAM_VALU || node_family(g, mmi) == FAM_DW) {
@@ -1256,7 +1414,7 @@ static mure_status run_group(mure_ctx* ctx, int gi, int s_begin, int s_end, uint
         gin.g0 = (int)e0; gin.C = nm.C; gin.P = (int)vP;
       }
       VirtualIn vin;
-      if (gr.virt) {
+      if (gr.virt || vc) {
         vin.cache = mmi_cache;
         vin.chmap = ctx->chmapv + gt.vchmap + (int64_t)cs0 * nm.C;
         vin.delta = where(mmi).p;
@@ -1267,6 +1425,17 @@ static mure_status run_group(mure_ctx* ctx, int gi, int s_begin, int s_end, uint
       std::set<int> done;
       for (int v = mmi + 1; v <= L; ++v) {
         if (done.count(v)) continue;
+        const auto ch = gt.chains.find(v);
+        if (chains && ch != gt.chains.end()) {
+          const bool first = vc && v == mmi + 1;
+          mure_status st = exec_chain(
+              ctx, ch->second,
+              [&](int p) -> Where { return first && p == mmi ? Where{mmi_cache, MODE_CACHE} : where(p); },
+              first ? &vin : nullptr, cs0, ns, cnt, (int)x0, true);
+          if (st != MURE_OK) return st;
+          v = ch->second.first.b;
+          continue;
+        }
         const Node& nd = g.nodes[v];
         std::vector<Where> ins;
         for (int k = 0; k < nd.n_in; ++k) ins.push_back(where(nd.in[k]));
@@ -1360,7 +1529,8 @@ static mure_status run_mutants_impl(mure_ctx* ctx, uint64_t* kill_bits_dev, int6
     // refuse before any device work if some cluster's smallest chunk does not fit
     for (int gi = 0; gi < (int)ctx->plan.groups.size(); ++gi) {
       const int ns = (int)ctx->plan.groups[gi].mutants.size();
-      const ChunkGeom cg = group_geometry(ctx, gi, ns, std::min(ws_bytes, ctx->max_ws_mb << 20));
+      // (the layer-by-layer chunk decides, whether or not chains would fit)
+      const ChunkGeom cg = group_geometry(ctx, gi, ns, std::min(ws_bytes, ctx->max_ws_mb << 20), false);
       if (cg.need_bytes > ws_bytes)
         return ctx->fail(MURE_E_NOMEM, "cluster " + std::to_string(gi) + " needs " + std::to_string(cg.need_bytes) +
                                            " bytes of workspace per chunk; the scratch array holds " +

@@ -213,6 +213,31 @@ std::vector<int> boundary(const Graph& g, int mmi) {
   return std::vector<int>(K.begin(), K.end());
 }
 
+void virtual_map(const Graph& g, const Plan& p, Group& gr) {
+  const int C = g.nodes[gr.mmi].c_out;
+  gr.T = 0;
+  if (gr.n_recompute > 0) {
+    if (gr.delta) {
+      for (int s = 0; s < gr.n_recompute; ++s)
+        gr.T = std::max(gr.T, (int)p.mutants[gr.mutants[s]].touched_list.size());
+    } else {
+      gr.T = C;
+    }
+  }
+  gr.vchmap.resize(gr.mutants.size() * C);
+  for (size_t s = 0; s < gr.mutants.size(); ++s) {
+    const MutantPlan& mp = p.mutants[gr.mutants[s]];
+    int* row = &gr.vchmap[s * C];
+    for (int c = 0; c < C; ++c) row[c] = mp.chmap[c];
+    if ((int)s < gr.n_recompute) {
+      if (gr.delta)
+        for (size_t t = 0; t < mp.touched_list.size(); ++t) row[mp.touched_list[t]] = -2 - (int)t;
+      else
+        for (int c = 0; c < C; ++c) row[c] = -2 - c;
+    }
+  }
+}
+
 std::string build_plan(const Graph& g, int n_mutants, const std::vector<Record>& recs, Plan& plan,
                        bool vanilla) {
   std::ostringstream err;
@@ -358,30 +383,7 @@ std::string build_plan(const Graph& g, int n_mutants, const std::vector<Record>&
       }
       gr.vhalo = ok && any;
     }
-    if (gr.virt || gr.vhalo) {
-      const int C = g.nodes[gr.mmi].c_out;
-      gr.T = 0;
-      if (gr.n_recompute > 0) {
-        if (gr.delta) {
-          for (int s = 0; s < gr.n_recompute; ++s)
-            gr.T = std::max(gr.T, (int)p.mutants[gr.mutants[s]].touched_list.size());
-        } else {
-          gr.T = C;
-        }
-      }
-      gr.vchmap.resize(gr.mutants.size() * C);
-      for (size_t s = 0; s < gr.mutants.size(); ++s) {
-        const MutantPlan& mp = p.mutants[gr.mutants[s]];
-        int* row = &gr.vchmap[s * C];
-        for (int c = 0; c < C; ++c) row[c] = mp.chmap[c];
-        if ((int)s < gr.n_recompute) {
-          if (gr.delta)
-            for (size_t t = 0; t < mp.touched_list.size(); ++t) row[mp.touched_list[t]] = -2 - (int)t;
-          else
-            for (int c = 0; c < C; ++c) row[c] = -2 - c;
-        }
-      }
-    }
+    if (gr.virt || gr.vhalo) virtual_map(g, p, gr);
     for (int k : gr.K) cache.insert(k);
     if (gr.n_recompute < (int)gr.mutants.size() || gr.delta || gr.virt) cache.insert(gr.mmi);
     const int gi = (int)p.groups.size();

@@ -180,6 +180,10 @@ struct Plan {
   int64_t macs_vanilla = 0, macs_memoized = 0, macs_algorithmic = 0, macs_executed = 0;
 };
 
+// Fills gr.T and gr.vchmap: each slot's view of mmi's output as cached
+// channels, zeros and compact delta channels.
+void virtual_map(const Graph& g, const Plan& p, Group& gr);
+
 // The ADD node fused into convolution v's epilogue (v's only reader, reading
 // it as in[0]), or -1.
 int fused_add_of(const Graph& g, int v);
