@@ -23,6 +23,15 @@
 // which ds_read_b128 serves without bank conflicts.  Within a chunk the
 // fragments of tap t + 1 are read before the MFMAs of tap t are issued.
 //
+// A wave's four M tiles are chosen so that a tile's fragment one tap row down is
+// the next tile's (HaloPx): a chunk reads 18 A fragments for 12 x 3 uses, at
+// addresses that are a register and a constant, instead of 36 with their
+// offsets worked out at each use.  With 36 + 18 reads per 72 MFMAs LDS had been
+// busy three quarters of the MFMA peak, and the address instructions as long.
+// All launches of a run: vgg (2,000 x 128) 62.0 -> 57.0 ms (993 -> 1,080
+// TFLOP/s; an 8192^3 library product reaches 1,320), the wide ResNet (1,000 x
+// 40) 170.9 -> 162.1 ms.  The reduction order is unchanged.
+//
 // The stages are fetched with direct global-to-LDS loads (16 bytes per lane,
 // landing at consecutive LDS addresses per instruction), so staging takes no
 // registers.  A load instruction fetches one halo block -- the two lanes of
@@ -102,8 +111,99 @@ __device__ __forceinline__ bool halo_decode(const ConvArgs& a, int t, HaloTile& 
   return true;
 }
 
+// Where the halo's pixels stand.  A wave's M tile i (i < 4) and a tap's row
+// dy read fragment F(i + dy): six row fragments per column step serve the 12
+// (tile, dy) pairs, so a tile's pixels are chosen for F(j + 1) to be F(j) one
+// row lower.  At W = 32 a tile is one row of the wave's four; at 64 half a row
+// of its four (two waves side by side); at 16 and 8 the rows i, i + 4 (, i +
+// 8, i + 12) of its 8 (16).  The rows of one fragment then stand 4 apart, and
+// the halo blocks of 32 pixels are filled so that they fall into different
+// parts of their blocks (a half wave reads 32 distinct 16-byte slots): row r
+// of image im goes to
+//   W >= 32: its place in the flattened rows;
+//   W = 16 (two rows a block): part bit 2 of r, flipped for the second image;
+//   W = 8 (four rows a block), images of 8 rows: part 2 (im & 1) + bit 2 of
+//     r, flipped for every other pair of images; taller images: part
+//     (r / 4 + im) mod 4;
+// of block 4 (r / (2 or 4 parts of 4 rows)) + r % 4 of its image(s).  The two
+// last halo rows of every image share the blocks from 16 on.
+struct HaloPx {
+  int im, r, x;
+};
+
+// pixel at place l (0 .. 31) of halo block q; im < 0: none
+template <int W>
+__device__ __forceinline__ HaloPx halo_px(int q, int l, int RI) {
+  constexpr int TR = 512 / W;
+  HaloPx p;
+  p.x = l % W;
+  if constexpr (W >= 32) {
+    const int hr = q * 32 / W;                         // one image per band
+    p.im = hr < RI + 2 ? 0 : -1;
+    p.r = hr;
+    p.x = (q * 32 + l) % W;
+  } else if constexpr (W == 16) {
+    const int part = l >> 4;
+    if (q < 16) {
+      p.im = RI == 16 ? q >> 3 : 0;
+      const int qq = RI == 16 ? q & 7 : q;
+      p.r = 8 * (qq >> 2) + (q & 3) + 4 * (part ^ (p.im & 1));
+    } else {
+      p.im = part < TR / RI ? part : -1;
+      p.r = RI + q - 16;
+    }
+  } else {
+    const int part = l >> 3;
+    if (RI == 8) {
+      const int P = q < 16 ? q >> 2 : 2 * ((q - 16) >> 1) + (part & 1);
+      p.im = 2 * P + (part >> 1);
+      p.r = q < 16 ? (q & 3) + 4 * ((part ^ P) & 1) : 8 + (q & 1);
+    } else if (q < 16) {
+      p.im = q / (RI / 4);
+      p.r = 16 * ((q % (RI / 4)) >> 2) + (q & 3) + 4 * ((part - p.im) & 3);
+    } else {
+      p.im = q < 18 && part < TR / RI ? part : -1;
+      p.r = RI + q - 16;
+    }
+  }
+  return p;
+}
+
+// byte offset in a stage of halo pixel (im, r, x), channel half h (the
+// inverse of halo_px)
+template <int W>
+__device__ __forceinline__ int halo_at(int im, int r, int x, int h, int RI) {
+  int block, slot;
+  if constexpr (W >= 32) {
+    const int px = r * W + x;
+    block = px >> 5;
+    slot = px & 31;
+  } else if constexpr (W == 16) {
+    const int part = r < RI ? ((r >> 2) ^ im) & 1 : im & 1;
+    block = r < RI ? im * (RI / 2) + (r >> 3) * 4 + (r & 3) : 16 + r - RI;
+    slot = part * 16 + x;
+  } else if (RI == 8) {
+    const int P = im >> 1;
+    block = r < 8 ? P * 4 + (r & 3) : 16 + (P >> 1) * 2 + r - 8;
+    slot = (2 * (im & 1) + (((r >> 2) ^ P) & 1)) * 8 + x;
+  } else {
+    block = r < RI ? im * (RI / 4) + (r >> 4) * 4 + (r & 3) : 16 + r - RI;
+    slot = (((r >> 2) + im) & 3) * 8 + x;
+  }
+  return block * 1024 + h * 512 + slot * 16;
+}
+
+// band pixel of row rho (0 .. 31) of a wave's M tile i
+template <int W>
+__device__ __forceinline__ int halo_m(int wave, int i, int rho) {
+  if constexpr (W == 64) return (4 * (wave >> 1) + i) * 64 + 32 * (wave & 1) + rho;
+  if constexpr (W == 32) return (4 * wave + i) * 32 + rho;
+  if constexpr (W == 16) return (8 * wave + i + 4 * (rho >> 4)) * 16 + (rho & 15);
+  return (16 * wave + i + 4 * (rho >> 3)) * 8 + (rho & 7);
+}
+
 // The lane's sources for this wave's load instructions q = wave + 4 s of a
-// tile.  q < NQ_HALO fills halo block q: pixels 32 q + (lane & 31), channel
+// tile.  q < NQ_HALO fills halo block q: pixel halo_px(q, lane & 31), channel
 // half lane >> 5, so the two lanes of a pixel read the chunk's 32 bytes from
 // one cache line; hs.h[s] is the element offset of that pixel's half from
 // the tile's input base hs.in0 at chunk 0 (-1: zeros), or with VIN (input
@@ -122,8 +222,8 @@ struct HaloSrc {
 };
 
 template <int W, int TN, bool VIN>
-__device__ __forceinline__ void halo_sources(const ConvArgs& a, const HaloTile& tl, int RI, int npx, int wave,
-                                             int lane, HaloSrc<W, TN>& hs) {
+__device__ __forceinline__ void halo_sources(const ConvArgs& a, const HaloTile& tl, int RI, int wave, int lane,
+                                             HaloSrc<W, TN>& hs) {
   using G = HaloGeo<W, TN>;
   const int ncol = a.cols ? a.ncols : a.Cout;
   hs.in0 = reinterpret_cast<const bf16_t*>(a.in.p) +
@@ -132,13 +232,13 @@ __device__ __forceinline__ void halo_sources(const ConvArgs& a, const HaloTile& 
 #pragma unroll
   for (int s = 0; s < HaloSrc<W, TN>::NH; ++s) {
     const int q = wave + 4 * s;
-    const int hh = lane >> 5, px = q * 32 + (lane & 31);
-    const int im = px / ((RI + 2) * W), rem = px % ((RI + 2) * W);
-    const int y = tl.y0 + rem / W - 1, x = rem % W;
+    const int hh = lane >> 5;
+    const HaloPx px = halo_px<W>(q, lane & 31, RI);
+    const int y = tl.y0 + px.r - 1;
     hs.h[s] = -1;
-    if (q < G::NQ_HALO && px < npx && tl.xi0 + im < a.nx && (unsigned)y < (unsigned)a.H)
-      hs.h[s] = VIN ? (tl.xi0 + im) * a.H * W + y * W + x
-                    : (int)(im * a.in.row_elems) + (y * W + x) * a.C + hh * 8;
+    if (q < G::NQ_HALO && px.im >= 0 && tl.xi0 + px.im < a.nx && (unsigned)y < (unsigned)a.H)
+      hs.h[s] = VIN ? (tl.xi0 + px.im) * a.H * W + y * W + px.x
+                    : (int)(px.im * a.in.row_elems) + (y * W + px.x) * a.C + hh * 8;
   }
   // weights: column n0 + lane % BN of the tile; with BN = 32 the upper half
   // wave reads the second channel half of each tap
@@ -179,10 +279,9 @@ __device__ __forceinline__ void halo_group_bases(const GroupIn& gi, int slot, in
 }
 
 // Issue the loads of the chunk at channel c0 (weight entries wc on from
-// chunk 0's) into the stage at st.  Lanes past the halo load nothing.
+// chunk 0's) into the stage at st.
 template <int W, int TN, bool VIN>
-__device__ __forceinline__ void halo_fetch(unsigned char* st, const HaloSrc<W, TN>& hs, int npx, int wave, int lane,
-                                           int c0, int wc, int Cout, const bf16_t* zp,
+__device__ __forceinline__ void halo_fetch(unsigned char* st, const HaloSrc<W, TN>& hs, int wave, int lane, int c0, int wc, int Cout, const bf16_t* zp,
                                            const bf16_t* const (&gb)[2], const int (&gst)[2]) {
   using G = HaloGeo<W, TN>;
 #pragma unroll
@@ -190,17 +289,15 @@ __device__ __forceinline__ void halo_fetch(unsigned char* st, const HaloSrc<W, T
     const int q = wave + 4 * s;
     if (q >= G::NQ) continue;
     if (q < G::NQ_HALO) {
-      if (q * 32 + (lane & 31) < npx) {
-        const int e = hs.h[s < HaloSrc<W, TN>::NH ? s : 0];
-        const bf16_t* p;
-        if constexpr (VIN) {
-          const int hh = lane >> 5;
-          p = e < 0 ? zp : gb[hh] + (int64_t)e * gst[hh];
-        } else {
-          p = e < 0 ? zp : hs.in0 + e + c0;
-        }
-        __builtin_amdgcn_global_load_lds((const void*)p, (lds_void*)(st + q * 1024), 16, 0, 0);
+      const int e = hs.h[s < HaloSrc<W, TN>::NH ? s : 0];
+      const bf16_t* p;
+      if constexpr (VIN) {
+        const int hh = lane >> 5;
+        p = e < 0 ? zp : gb[hh] + (int64_t)e * gst[hh];
+      } else {
+        p = e < 0 ? zp : hs.in0 + e + c0;
       }
+      __builtin_amdgcn_global_load_lds((const void*)p, (lds_void*)(st + q * 1024), 16, 0, 0);
     } else {
       // entries e = 64 (q - NQ_HALO) + lane: tap e / 2BN, half (e / BN) & 1
       const int e0 = (q - G::NQ_HALO) * 64;
@@ -212,98 +309,69 @@ __device__ __forceinline__ void halo_fetch(unsigned char* st, const HaloSrc<W, T
   }
 }
 
-// Byte offset in a stage of halo pixel p, channel half h: the halo is
-// stored in blocks of 32 pixels, [block][half][32][8].
-__device__ __forceinline__ int halo_addr(int p, int h) { return (p >> 5) * 1024 + h * 512 + (p & 31) * 16; }
-
-// Fragment bases: lane row (lane & 31) of M tile i is band pixel m, its 8 k
-// are channels 8 h of the chunk (h = lane >> 5).  The tap (dy, dx) reads halo
-// pixel hp + (dy + 1) W + dx, where hp is the pixel's column in the halo row
-// above it.  A.r[i] is the entry of hp; for W >= 32 the rows below are whole
-// blocks further, for W <= 16 a row step stays in the block or moves to the
-// next one (halo_row_step).  A step of one column moves 16 bytes within a
-// block, or 528 across one (x = 31 | 32 at W = 64); cross bit i: the pixel is
-// the last of its block, bit 4 + i: the first.  edge bit i: the pixel is in
-// column 0, bit 4 + i: in column W - 1.  A tap that would read column -1 or
-// W reads the zero block instead, at the offset it would have had in its own
-// block: the half wave's 32 lanes then still hit 32 distinct 16-byte slots
-// (one shared zero entry cost a bank conflict on every such read).
+// A lane's fragment addresses in a stage, per column step dx: F(0) and F(4)
+// (F(j) and F(4 + j) stand j steps further; for W >= 32 F(4) is four steps from
+// F(0)).  A tap that would read column -1 or W reads a zero block instead, at
+// the offset it would have had in its own block, with a step of 0: the half
+// wave's 32 lanes then still hit 32 distinct 16-byte slots (one shared zero
+// entry cost a bank conflict on every such read).  A step of one column moves
+// 16 bytes within a block, or 528 across one (x = 31 | 32 at W = 64).
 template <int W>
 struct HaloA {
-  int r[4];
-  int edge, cross;
+  static constexpr int STEP = W == 64 ? 2048 : 1024;
+  int b[3], c[3], s[3];
+  __device__ __forceinline__ int at(int j, int dx) const {
+    if (dx == 1) return j < 4 || W >= 32 ? b[1] + j * STEP : c[1] + (j - 4) * STEP;
+    return j < 4 || W >= 32 ? b[dx] + j * s[dx] : c[dx] + (j - 4) * s[dx];
+  }
 };
 
-// halo_addr(p + k W) from a = halo_addr(p) (k = 1, 2), from the bits of a
-// that hold p % 32: the step leaves the block when p % 32 + k W >= 32.
-template <int W>
-__device__ __forceinline__ int halo_row_step(int a, int k) {
-  if constexpr (W >= 32) return a + k * (W / 32) * 1024;
-  const int d = k * W;                                   // pixels: 8, 16 or 32
-  if (d == 32) return a + 1024;
-  if (d == 16) return a + 256 + ((a & 256) << 1);        // bit 4 of p: 16 -> next block (+1024 - 256)
-  // d == 8: p % 32 >= 24 (bits 3 and 4 of p) -> next block (+1024 - 384)
-  return a + 128 + ((a & (a >> 1) & 128) << 2);
-}
 template <int W, int TN>
 __device__ __forceinline__ void halo_abase(int wave, int lane, int RI, HaloA<W>& A) {
-  const int h = lane >> 5;
-  A.edge = 0;
-  A.cross = 0;
+  using G = HaloGeo<W, TN>;
+  const int h = lane >> 5, rho = lane & 31;
+  const int m = halo_m<W>(wave, 0, rho), row = m / W, x = m % W;
+  const int im = row / RI, r = row % RI;               // F(0): tile 0 one row up, halo row r
+  A.b[1] = halo_at<W>(im, r, x, h, RI);
+  A.c[1] = W >= 32 ? 0 : halo_at<W>(im, r + 4, x, h, RI);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = wave * 128 + i * 32 + (lane & 31);
-    const int row = m / W, x = m % W;
-    const int hp = ((row / RI) * (RI + 2) + row % RI) * W + x;
-    A.r[i] = halo_addr(hp, h);
-    A.edge |= (x == 0 ? 1 : 0) << i;
-    A.edge |= (x == W - 1 ? 1 : 0) << (4 + i);
-    A.cross |= ((hp & 31) == 31 ? 1 : 0) << i;
-    A.cross |= ((hp & 31) == 0 ? 1 : 0) << (4 + i);
+  for (int dx = 0; dx < 3; dx += 2) {
+    const int d = dx - 1;
+    const bool edge = dx == 0 ? x == 0 : x == W - 1;
+    int step = 16 * d;
+    if (W == 64 && (dx == 0 ? rho == 0 : rho == 31)) step += 512 * d;
+    A.s[dx] = edge ? 0 : HaloA<W>::STEP;
+    A.b[dx] = edge ? G::HZERO | ((A.b[1] + 16 * d) & 1023) : A.b[1] + step;
+    A.c[dx] = edge ? G::HZERO | ((A.c[1] + 16 * d) & 1023) : A.c[1] + step;
   }
 }
 
 // The nine k-steps of the chunk staged at st (B: column j 32 + (lane & 31),
-// half h).
+// half h): 18 A and 9 TN B fragment reads for 36 TN MFMAs.  The reads of tap t
+// + 1 are issued before the MFMAs of tap t.
 template <int W, int TN>
 __device__ __forceinline__ void halo_mma(const unsigned char* st, const HaloA<W>& A, int bbase, v16f (&acc)[4][TN]) {
   using G = HaloGeo<W, TN>;
-  v8bf fa[2][4], fb[2][TN];
-  auto load = [&](int t, int p) {
-    const int dy = t / 3, dx = t % 3 - 1;
+  v8bf fa[6][3], fb[2][TN];
+  auto load = [&](int t) {
+    const int dy = t / 3, dx = t % 3;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      int off = A.r[i];
-      if (W < 32 && dy != 0) {
-        // recomputed at each use: kept, the row steps would hold 4-8 more registers
-        asm volatile("" : "+v"(off));
-        off = halo_row_step<W>(off, dy);
-      } else if (dy != 0) {
-        off = halo_row_step<W>(off, dy);
-      }
-      off += dx * 16;
-      // a column step crosses a block only inside a 64-pixel row; for
-      // W <= 32 the block edges are image edges, which read zeros
-      if constexpr (W == 64) {
-        if (dx > 0 && ((A.cross >> i) & 1)) off += 512;
-        if (dx < 0 && ((A.cross >> (4 + i)) & 1)) off -= 512;
-      }
-      if (dx != 0 && ((A.edge >> (i + (dx > 0 ? 4 : 0))) & 1)) off = G::HZERO | (off & 1023);
-      fa[p][i] = *reinterpret_cast<const v8bf*>(st + off);
-    }
+    for (int j = dy == 0 ? 0 : 3 + dy; j < 4 + dy; ++j)
+      fa[j][dx] = *reinterpret_cast<const v8bf*>(st + A.at(j, dx));
 #pragma unroll
-    for (int j = 0; j < TN; ++j) fb[p][j] = *reinterpret_cast<const v8bf*>(st + bbase + (t * 2 * G::BN + j * 32) * 16);
+    for (int j = 0; j < TN; ++j)
+      fb[t & 1][j] = *reinterpret_cast<const v8bf*>(st + bbase + (t * 2 * G::BN + j * 32) * 16);
   };
-  load(0, 0);
+  load(0);
 #pragma unroll
   for (int t = 0; t < 9; ++t) {
-    if (t < 8) load(t + 1, (t + 1) & 1);
+    if (t < 8) load(t + 1);
     __builtin_amdgcn_sched_barrier(0);                 // keep those reads ahead of the MFMAs
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[t & 1][i], fb[t & 1][j], acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i + t / 3][t % 3], fb[t & 1][j], acc[i][j], 0, 0, 0);
   }
 }
 
@@ -333,10 +401,9 @@ __device__ __forceinline__ void halo_round(const ConvArgs& a, const HaloTile& tl
   }
 }
 
-// A wave's 128 rounded pixels into the staging tile Os ([pixel][OLD]) from
-// row r0 on.
+// A wave's 128 rounded pixels into the staging tile Os ([band pixel][OLD]).
 template <int W, int TN>
-__device__ __forceinline__ void halo_stage(bf16_t* Os, int r0, int lane, const uint32_t (&ob)[4][TN][8]) {
+__device__ __forceinline__ void halo_stage(bf16_t* Os, int wave, int lane, const uint32_t (&ob)[4][TN][8]) {
   using G = HaloGeo<W, TN>;
   const int h = lane >> 5;
 #pragma unroll
@@ -345,7 +412,7 @@ __device__ __forceinline__ void halo_stage(bf16_t* Os, int r0, int lane, const u
     for (int i = 0; i < 4; ++i)
 #pragma unroll
       for (int e = 0; e < 16; e += 2) {
-        const int r = r0 + i * 32 + (e >> 2) * 8 + h * 4 + (e & 3);
+        const int r = halo_m<W>(wave, i, (e >> 2) * 8 + h * 4 + (e & 3));
         const uint32_t v = ob[i][j][e >> 1];
         Os[r * G::OLD + j * 32 + (lane & 31)] = (bf16_t)v;
         Os[(r + 1) * G::OLD + j * 32 + (lane & 31)] = (bf16_t)(v >> 16);
@@ -439,11 +506,14 @@ __device__ __forceinline__ void halo_store_rows(const ConvArgs& a, const HaloTil
 }
 // ---- epilogue in two passes for an identity shortcut ----
 // Pass P stores the 256 band pixels of M tiles 2P and 2P + 1 of every wave;
-// its local pixel ml is band pixel halo_pass_pixel(P, ml).  Pass 0's
+// its local pixel ml is band pixel halo_pass_pixel<W>(P, ml).  Pass 0's
 // shortcut rows are brought into the stage the last chunk left free by direct
 // loads issued with that chunk's MFMAs; pass 1's are loaded into registers
 // once pass 0 is staged, under pass 0's stores.
-__device__ __forceinline__ int halo_pass_pixel(int P, int ml) { return (ml >> 6) * 128 + P * 64 + (ml & 63); }
+template <int W>
+__device__ __forceinline__ int halo_pass_pixel(int P, int ml) {
+  return halo_m<W>(ml >> 6, 2 * P + ((ml >> 5) & 1), ml & 31);
+}
 
 // The identity shortcut's channels n .. n + 7 at output pixel (xi, y, x): from
 // whole rows, or (VSKIP) read in channel groups, from the shared cache or from
@@ -475,7 +545,7 @@ __device__ __forceinline__ void halo_skip_dma(const ConvArgs& a, const HaloTile&
     const int pc = q * 64 + lane, ml = pc / G::VPR, vc = pc % G::VPR;
     const int n = tl.n0 + vc * 8;
     int xi, y, x;
-    halo_pixel<W>(tl, rsh, halo_pass_pixel(0, ml), xi, y, x);
+    halo_pixel<W>(tl, rsh, halo_pass_pixel<W>(0, ml), xi, y, x);
     const bf16_t* src = zp;
     if (n < a.Cout && xi < a.nx) src = halo_skip_at<W, VSKIP>(a, tl, xi, y, x, n, skip_e);
     __builtin_amdgcn_global_load_lds((const void*)src, (lds_void*)(F + q * 1024), 16, 0, 0);
@@ -491,7 +561,7 @@ __device__ __forceinline__ void halo_skip_pass1(const ConvArgs& a, const HaloTil
   for (int k = 0; k < G::VPR; ++k) {
     const int idx = tid + G::NT * k, ml = idx / G::VPR, n = tl.n0 + (idx % G::VPR) * 8;
     int xi, y, x;
-    halo_pixel<W>(tl, rsh, halo_pass_pixel(1, ml), xi, y, x);
+    halo_pixel<W>(tl, rsh, halo_pass_pixel<W>(1, ml), xi, y, x);
     sk[k] = v4u{0u, 0u, 0u, 0u};
     if (n < a.Cout && xi < a.nx) sk[k] = *reinterpret_cast<const v4u*>(halo_skip_at<W, VSKIP>(a, tl, xi, y, x, n, skip_e));
   }
@@ -535,7 +605,7 @@ __device__ __forceinline__ void halo_store_pass(const ConvArgs& a, const HaloTil
     const int n = tl.n0 + vc * 8;
     if (n >= a.Cout) continue;
     int xi, y, x;
-    halo_pixel<W>(tl, rsh, halo_pass_pixel(P, ml), xi, y, x);
+    halo_pixel<W>(tl, rsh, halo_pass_pixel<W>(P, ml), xi, y, x);
     if (xi >= a.nx) continue;
     v4u val = *reinterpret_cast<const v4u*>(&Os[ml * G::OLD + vc * 8]);
     const v4u sv = P == 0 ? *reinterpret_cast<const v4u*>(F + idx * 16) : sk[k];
@@ -574,7 +644,6 @@ void conv_halo_kernel(ConvArgs a) {
   const int ncol = a.cols ? a.ncols : a.Cout;
   const int RI = a.H < G::TR ? a.H : G::TR;
   const int rsh = 31 - __builtin_clz((unsigned)RI);
-  const int npx = (G::TR / RI) * (RI + 2) * W;
   const bf16_t* const zp = reinterpret_cast<const bf16_t*>(g_halo_zero);
   const int nch = a.C / 16;
   // an identity shortcut of the whole tile's rows: the two-pass epilogue
@@ -585,7 +654,7 @@ void conv_halo_kernel(ConvArgs a) {
   static_assert(G::STAGE % 1024 == 0 && G::HZERO % 1024 == 0, "stages and zero blocks are 1024-byte aligned");
 
   HaloSrc<W, TN> hs;
-  halo_sources<W, TN, VIN>(a, tl, RI, npx, wave, lane, hs);
+  halo_sources<W, TN, VIN>(a, tl, RI, wave, lane, hs);
   const bf16_t* gb[2] = {nullptr, nullptr};
   int gst[2] = {0, 0};
   int skip_e = -1;
@@ -609,12 +678,12 @@ void conv_halo_kernel(ConvArgs a) {
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
   if constexpr (VIN) halo_group_bases(a.gin, tl.slot, a.nx, 0, gb, gst);
-  halo_fetch<W, TN, VIN>(smem, hs, npx, wave, lane, 0, 0, a.Cout, zp, gb, gst);
+  halo_fetch<W, TN, VIN>(smem, hs, wave, lane, 0, 0, a.Cout, zp, gb, gst);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   for (int c = 0; c + 1 < nch; ++c) {
     if constexpr (VIN) halo_group_bases(a.gin, tl.slot, a.nx, (c + 1) * 16, gb, gst);
-    halo_fetch<W, TN, VIN>(smem + ((c + 1) & 1) * G::STAGE, hs, npx, wave, lane, (c + 1) * 16,
+    halo_fetch<W, TN, VIN>(smem + ((c + 1) & 1) * G::STAGE, hs, wave, lane, (c + 1) * 16,
                            (c + 1) * 16 * wstep, a.Cout, zp, gb, gst);
     halo_mma<W, TN>(smem + (c & 1) * G::STAGE, A, bbase, acc);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -645,7 +714,7 @@ void conv_halo_kernel(ConvArgs a) {
   {
     uint32_t ob[4][TN][8];
     halo_round<TN>(a, tl, lane, acc, ob);
-    halo_stage<W, TN>(reinterpret_cast<bf16_t*>(smem), wave * 128, lane, ob);
+    halo_stage<W, TN>(reinterpret_cast<bf16_t*>(smem), wave, lane, ob);
   }
   v4u skipv[NV];
   if (!a.cols && !a.pool && a.add_mode) halo_skip<W, TN, BM, VIN && !VSKIP>(a, tl, rsh, 0, tid, skipv);
