@@ -14,7 +14,7 @@
 // leave the lane.
 //
 // lstm_wide_kernel: for layers whose weights do not fit in LDS.  A block owns
-// 64 rows of one slot with H / 16 waves; wave w owns units 16w .. 16w + 15, all
+// 64 rows (16 in small launches) of one slot with H / 16 waves; wave w owns units 16w .. 16w + 15, all
 // four gates (64 GEMM columns), and holds its weight columns in registers.
 // The step input [x_t, h_{t-1}, 1] lives in LDS as [k / 4][row][4], so the A
 // fragments of a k-step are 256 contiguous bytes; two such tiles alternate by
@@ -54,23 +54,27 @@ __global__ __launch_bounds__(256) void embed_kernel(SeqArgs a, DivU32 dd, DivU32
 // Gate activations from the hardware exponential: sigmoid(z) = 1/(1 + e^-z)
 // and tanh(z) = 2 sigmoid(2z) - 1 (a few ulp from the correctly rounded
 // values; every launch of a layer uses the same formulas).
-__device__ __forceinline__ float sigmoidf_(float z) { return __fdividef(1.f, 1.f + __expf(-z)); }
+// The reciprocal is the hardware's with one Newton step (within a rounding of
+// the exact quotient; the compiler's division takes three times as many
+// instructions), fixed up for an infinite denominator (0) and a NaN.
+__device__ __forceinline__ float sig_rcp(float d) {
+  const float r = __builtin_amdgcn_rcpf(d);
+  return __builtin_amdgcn_div_fixupf(fmaf(fmaf(-d, r, 1.f), r, r), d, 1.f);
+}
+__device__ __forceinline__ float sigmoidf_(float z) { return sig_rcp(1.f + __expf(-z)); }
 __device__ __forceinline__ float tanhf_(float z) { return 2.f * sigmoidf_(2.f * z) - 1.f; }
 
-// Zero bytes that the wide kernel's rows past the last input read.
-static __device__ __attribute__((aligned(16))) v4f g_lstm_zero[1] = {};
-__device__ __forceinline__ const float* lstm_zero() { return reinterpret_cast<const float*>(g_lstm_zero); }
-
-// Block b -> (slot, block of 64 input rows).  Block b runs on XCD b % 8; on
+// Block b -> (slot, block of R input rows).  Block b runs on XCD b % 8; on
 // one XCD consecutive blocks take every slot of one row block in turn, so a
 // row block of a shared input (a prefix-cache tensor, read by every slot)
 // comes from HBM once and the other slots' reads hit that XCD's L2.  false:
 // padding of that order.
+template <int R>
 __device__ __forceinline__ bool lstm_decode(const SeqArgs& a, int& sl, int& rb) {
   const int b = (int)blockIdx.x, turn = b >> 3;
   rb = (turn / a.nslots) * 8 + (b & 7);
   sl = a.slot0 + turn % a.nslots;
-  return rb * 64 < a.nx;
+  return rb * R < a.nx;
 }
 
 template <int HT>                                      // H = 16 * HT units
@@ -79,7 +83,7 @@ __global__ __launch_bounds__(256) void lstm_kernel(SeqArgs a) {
   constexpr int H = 16 * HT, NT = 4 * HT, NS = 4 * H + 16;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int sl, rb;
-  if (!lstm_decode(a, sl, rb)) return;
+  if (!lstm_decode<64>(a, sl, rb)) return;
   const int D = a.D, K = D + H + 1;
   const int KP = lstm_kpad(D, H), KA = lstm_ka(D, H);
   float* Ws = lsm;                                     // [KP][NS]
@@ -206,17 +210,27 @@ __global__ __launch_bounds__(256) void lstm_kernel(SeqArgs a) {
 
 
 // KS k-steps of 4 (K = D + H + 1 padded with zero weights to 4 KS; the
-// launcher rounds the needed steps up to a multiple of 4).
-template <int KS>
+// launcher rounds the needed steps up to a multiple of 4, and the rounding's
+// whole steps are skipped), 16 RT rows per block.
+//
+// The MFMAs of a step and its gates run one after the other on purpose: the
+// fp32 MFMA does not overlap with vector instructions (32 clocks alone, 46 with
+// one vector instruction behind each, 58 with four; gates interleaved with the
+// next step's x part took 14 % longer than in a run of their own).  A step of
+// rnn_imdb's first layer is 49 k-steps of 16 MFMAs, 25,100 clocks, and what
+// is left to gain is in the vector instructions: the gates' reciprocals and
+// the stores' addresses.
+template <int KS, int RT>
 __global__ __launch_bounds__(256, 1) void lstm_wide_kernel(SeqArgs a) {
   extern __shared__ __attribute__((aligned(16))) float lsm[];
   typedef __attribute__((address_space(3))) void lds_void;
+  constexpr int ROWS = 16 * RT, TS = ROWS * 4;         // rows, floats per k-step of a tile
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int NW = (int)blockDim.x / 64;                 // = H / 16
   int sl, rb;
-  if (!lstm_decode(a, sl, rb)) return;
-  const int D = a.D, H = a.H, K = D + H + 1, DS = D / 4;
-  // LDS: two step tiles [KS][64][4]: [x_t, h_{t-1}, 1, zeros] of step t in
+  if (!lstm_decode<ROWS>(a, sl, rb)) return;
+  const int D = a.D, H = a.H, K = D + H + 1, DS = D / 4, NS = (K + 3) / 4;
+  // LDS: two step tiles [KS][ROWS][4]: [x_t, h_{t-1}, 1, zeros] of step t in
   // tile t % 2
   const float* __restrict__ Wt = reinterpret_cast<const float*>(a.wtab[sl]);
   const int unit = wave * 16 + (lane & 15);
@@ -230,71 +244,74 @@ __global__ __launch_bounds__(256, 1) void lstm_wide_kernel(SeqArgs a) {
       wreg[s][q] = k < K ? Wt[((int64_t)unit * 4 + q) * K + k] : 0.f;
     }
   // both tiles: h = 0, the bias input 1 (k = D + H), zero padding (x_0 is loaded below)
-  for (int e = tid; e < 2 * (KS - DS) * 256; e += NW * 64) {
-    const int b = e / ((KS - DS) * 256), r = e % ((KS - DS) * 256);
-    const int k = D + (r >> 8) * 4 + (r & 3);
-    lsm[(b * KS + DS) * 256 + r] = k == D + H ? 1.f : 0.f;
+  for (int e = tid; e < 2 * (KS - DS) * TS; e += NW * 64) {
+    const int b = e / ((KS - DS) * TS), r = e % ((KS - DS) * TS);
+    const int k = D + (r / TS) * 4 + (r & 3);
+    lsm[(b * KS + DS) * TS + r] = k == D + H ? 1.f : 0.f;
   }
-  const int xi0 = rb * 64;
-  const float* __restrict__ X = reinterpret_cast<const float*>(a.in.p);
-  float* __restrict__ Y = reinterpret_cast<float*>(a.out);
-  auto in_row = [&](int xi) {
-    return a.in.mode == MODE_BUF ? (int64_t)sl * a.nx + xi : (int64_t)a.x0 + xi;
-  };
-  auto out_row = [&](int xi) {
-    return a.out_mode == MODE_BUF ? (int64_t)sl * a.nx + xi : (int64_t)a.x0 + xi;
-  };
-  // x_t into tile b: instruction j (channels 4j .. 4j + 3 of the 64 rows),
-  // lane = row; rows past nx read the zero page
-  const float* xsrc = xi0 + lane < a.nx ? X + in_row(xi0 + lane) * a.in.row_elems : nullptr;
+  const int xi0 = rb * ROWS;
+  // the block's rows are neighbours in either mode
+  const float* __restrict__ X =
+      reinterpret_cast<const float*>(a.in.p) + row_at(a.in.mode, sl, xi0, a.nx, a.x0) * a.in.row_elems;
+  float* __restrict__ Y = reinterpret_cast<float*>(a.out) + row_at(a.out_mode, sl, xi0, a.nx, a.x0) * a.out_row;
+  const int left = a.nx - xi0;                         // rows of the block that exist
+  // x_t into tile b: load instruction j fetches 64 / ROWS k-steps of every row
+  // (channels 4 s .. 4 s + 3 of row lane % ROWS); rows past nx repeat the last
+  // one and are not stored
+  constexpr int KPI = 64 / ROWS;
+  const int xk = lane / ROWS;
+  const float* const xsrc = X + (int64_t)min(lane % ROWS, left - 1) * a.in.row_elems + 4 * xk;
   auto fetch_x = [&](int t, int b) {
-    for (int j = wave; j < DS; j += NW)
-      __builtin_amdgcn_global_load_lds((const void*)(xsrc ? xsrc + (int64_t)t * D + 4 * j : lstm_zero()),
-                                       (lds_void*)(lsm + (b * KS + j) * 256), 16, 0, 0);
+    for (int j = wave; j * KPI < DS; j += NW)
+      if (j * KPI + xk < DS)
+        __builtin_amdgcn_global_load_lds((const void*)(xsrc + (int64_t)t * D + 4 * j * KPI),
+                                         (lds_void*)(lsm + (b * KS + j * KPI) * TS), 16, 0, 0);
   };
   fetch_x(0, 0);
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 
-  float cst[4][4];
+  float cst[RT][4];
 #pragma unroll
-  for (int i = 0; i < 4; ++i)
+  for (int i = 0; i < RT; ++i)
 #pragma unroll
     for (int e = 0; e < 4; ++e) cst[i][e] = 0.f;
+  const int r0 = (lane >> 4) * 4;                      // the lane's rows: 16 i + r0 + e
   for (int t = 0; t < a.T; ++t) {
     const int b = t & 1;
     // x_{t+1} and h_t go to the other tile, which no wave reads during step t
     if (t + 1 < a.T) fetch_x(t + 1, b ^ 1);
     // z = [x_t, h_{t-1}, 1] W^T for the wave's 64 columns, k in steps of 4;
     // A fragment: row 16 i + (lane & 15), k = 4 s + (lane >> 4)
-    v4f acc[4][4];
+    v4f acc[RT][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
       for (int q = 0; q < 4; ++q) acc[i][q] = v4f{0.f, 0.f, 0.f, 0.f};
-    const float* at = lsm + b * KS * 256 + (lane & 15) * 4 + (lane >> 4);
+    const float* at = lsm + b * KS * TS + (lane & 15) * 4 + (lane >> 4);
     // the fragments of k-step s + 1 are read before the MFMAs of step s
-    float av[2][4];
+    float av[2][RT];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) av[0][i] = at[i * 64];
+    for (int i = 0; i < RT; ++i) av[0][i] = at[i * 64];
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
+      if (s > KS - 4 && s >= NS) break;                // a step of padding only
       if (s + 1 < KS) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) av[(s + 1) & 1][i] = at[(s + 1) * 256 + i * 64];
+        for (int i = 0; i < RT; ++i) av[(s + 1) & 1][i] = at[(s + 1) * TS + i * 64];
       }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < RT; ++i)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
           acc[i][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[s & 1][i], wreg[s][q], acc[i][q], 0, 0, 0);
     }
-    // gates of unit `unit`, rows 16 i + 4 (lane >> 4) + e
-    float* hn = lsm + ((b ^ 1) * KS + DS + (unit >> 2)) * 256 + (unit & 3);
-    float hv[4][4];
+    // gates of unit `unit`, rows 16 i + r0 + e
+    float* hn = lsm + ((b ^ 1) * KS + DS + (unit >> 2)) * TS + (unit & 3);
+    float hv[RT][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < RT; ++i)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const float ig = sigmoidf_(acc[i][0][e]);
@@ -304,18 +321,17 @@ __global__ __launch_bounds__(256, 1) void lstm_wide_kernel(SeqArgs a) {
         const float c = fmaf(fg, cst[i][e], ig * gg);
         cst[i][e] = c;
         const float h = og * tanhf_(c);
-        hn[(i * 16 + (lane >> 4) * 4 + e) * 4] = h;
+        hn[(i * 16 + r0 + e) * 4] = h;
         hv[i][e] = h;
       }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // x_{t+1} has landed
     if (a.seq || t + 1 == a.T) {
+      float* const y = Y + (int64_t)(a.seq ? t : 0) * H + r0 * a.out_row + unit;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int xi = xi0 + i * 16 + (lane >> 4) * 4 + e;
-          if (xi < a.nx) Y[out_row(xi) * a.out_row + (int64_t)(a.seq ? t : 0) * H + unit] = hv[i][e];
-        }
+        for (int e = 0; e < 4; ++e)
+          if (i * 16 + r0 + e < left) y[(i * 16 + e) * a.out_row] = hv[i][e];
     }
     __syncthreads();                                   // h_t and x_{t+1} in place
   }
@@ -335,19 +351,38 @@ hipError_t launch_embed(const SeqArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Rows per block of the wide kernel.  One block runs on a CU (its weights take
+// the registers of a wave per SIMD), so a launch takes ceil(blocks / 256) turns
+// of about 16 RT rows' MFMAs plus a part that does not shrink with the rows (LDS
+// and barrier latency, about half of 16 rows' MFMAs): 2,500 inputs of one slot
+// took 1.1 ms with 64 rows (40 blocks on 256 CUs) and 0.45 ms with 16.
+static int lstm_wide_rows(int nx, int nslots) {
+  auto turns = [&](int rt) {
+    const int64_t blocks = (int64_t)((nx + 16 * rt - 1) / (16 * rt)) * nslots;
+    return (double)((blocks + 255) / 256) * (rt + 0.5);
+  };
+  return turns(1) < turns(4) ? 1 : 4;
+}
+
 hipError_t launch_lstm(const SeqArgs& a, hipStream_t s) {
   if (a.nslots <= 0 || a.nx <= 0) return hipSuccess;
   if (a.H % 16 || a.H < 16 || a.H > 64 || a.nslots > 65535) return hipErrorInvalidValue;
-  const int64_t nblk = ((int64_t)(a.nx + 63) / 64 + 7) / 8 * 8 * a.nslots;
+  const bool wide = lstm_uses_wide(a.D, a.H);
+  const int rt = wide ? lstm_wide_rows(a.nx, a.nslots) : 4, rows = 16 * rt;
+  const int64_t nblk = ((int64_t)(a.nx + rows - 1) / rows + 7) / 8 * 8 * a.nslots;
   if (nblk >= INT32_MAX) return hipErrorInvalidValue;
   const dim3 grid((unsigned)nblk);
-  if (lstm_uses_wide(a.D, a.H)) {
+  if (wide) {
     if (!lstm_wide_fits(a.D, a.H) || a.in.row_elems % 4) return hipErrorInvalidValue;
     const int ks = lstm_wide_ks(a.D, a.H);
-    const size_t lds = (size_t)lstm_wide_lds_bytes(a.D, a.H);
+    const size_t lds = (size_t)lstm_wide_lds_bytes(a.D, a.H) / 4 * rt;
     const dim3 block(64 * (a.H / 16));
     switch (ks) {
-#define MURE_LSTM_WIDE(n) case n: hipLaunchKernelGGL(lstm_wide_kernel<n>, grid, block, lds, s, a); break;
+#define MURE_LSTM_WIDE(n)                                                              \
+  case n:                                                                              \
+    if (rt == 1) hipLaunchKernelGGL((lstm_wide_kernel<n, 1>), grid, block, lds, s, a); \
+    else hipLaunchKernelGGL((lstm_wide_kernel<n, 4>), grid, block, lds, s, a);         \
+    break;
       MURE_LSTM_WIDE(8) MURE_LSTM_WIDE(12) MURE_LSTM_WIDE(16) MURE_LSTM_WIDE(20) MURE_LSTM_WIDE(24)
       MURE_LSTM_WIDE(28) MURE_LSTM_WIDE(32) MURE_LSTM_WIDE(36) MURE_LSTM_WIDE(40) MURE_LSTM_WIDE(44)
       MURE_LSTM_WIDE(48) MURE_LSTM_WIDE(52)
