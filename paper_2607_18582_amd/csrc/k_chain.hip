@@ -571,20 +571,29 @@ __device__ __forceinline__ void add_rows(const Blk& k, const ChainOp& o) {
 }
 
 // GAP: the pixels summed in order in float32, then scaled, as gap_kernel does.
+// One (image, 64 channels) per wave at a time: image after image in the whole
+// block leaves all but a few waves idle where the layer is narrow (14k of a
+// chain's clocks for 8 images of 64 channels; a pass of resnet20 47.4 -> 46.3 ms, of
+// mobilenetv2 48.0 -> 47.6).
 __device__ __forceinline__ void gap_rows(const Blk& k, const ChainOp& o, const ChainArgs& a, const ChainBuf& bf) {
-  const int P = 1 << o.lp;
-  for (int img = 0; img < k.cnt; ++img) {
-    const unsigned char* const in = k.sm + img * k.arena + o.in.off;
-    const int64_t row = row_at(bf.mode, k.slot, k.xi0 + img, a.nx, a.x0);
-    for (int c = k.tid; c < o.C; c += NT) {
-      float s = 0.f;
-#pragma unroll 8
-      for (int q = 0; q < P; ++q) {
-        const int p = t_px(o.in, q >> o.lw, q & ((1 << o.lw) - 1));
-        s += bf2f(*reinterpret_cast<const bf16_t*>(in + p * o.in.pxb + ((2 * c) ^ t_swz(o.in, p))));
-      }
-      reinterpret_cast<bf16_t*>(bf.p)[row * bf.row_elems + c] = f2bf(s * (1.0f / (float)P));
+  const int P = 1 << o.lp, cw = (o.C + 63) >> 6;       // waves per image
+  int img = 0, c0 = k.wave;
+  for (;; c0 += CHAIN_WAVES) {
+    while (c0 >= cw) {
+      c0 -= cw;
+      if (++img >= k.cnt) return;
     }
+    const int c = c0 * 64 + k.lane;
+    if (c >= o.C) continue;
+    const unsigned char* const in = k.sm + img * k.arena + o.in.off;
+    float s = 0.f;
+#pragma unroll 8
+    for (int q = 0; q < P; ++q) {
+      const int p = t_px(o.in, q >> o.lw, q & ((1 << o.lw) - 1));
+      s += bf2f(*reinterpret_cast<const bf16_t*>(in + p * o.in.pxb + ((2 * c) ^ t_swz(o.in, p))));
+    }
+    const int64_t row = row_at(bf.mode, k.slot, k.xi0 + img, a.nx, a.x0);
+    reinterpret_cast<bf16_t*>(bf.p)[row * bf.row_elems + c] = f2bf(s * (1.0f / (float)P));
   }
 }
 }  // namespace
