@@ -363,7 +363,8 @@ hipError_t launch_kill(const KillArgs& a, hipStream_t s);
 hipError_t launch_labels(const LabelArgs& a, hipStream_t s);
 hipError_t launch_score(const ScoreArgs& a, int n_mutants, hipStream_t s);
 hipError_t launch_group_patch(const GroupPatchArgs& a, hipStream_t s);
-hipError_t launch_cow(const CowArgs* d_args, int n_copies, const DevRecord* d_recs,
+// max_bytes, max_fan_in: of the largest copy's weights, of any copy
+hipError_t launch_cow(const CowArgs* d_args, int n_copies, int64_t max_bytes, int64_t max_fan_in, const DevRecord* d_recs,
                       const float* d_noise, int dtype, hipStream_t s);
 hipError_t launch_copy_rows(const TensorArg& src, void* dst, int64_t rows, int nx, int x0,
                             int esize, hipStream_t s);

@@ -1054,8 +1054,13 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
     ctx->chmapv = reinterpret_cast<int32_t*>(d + o_chmap);
     ctx->colv = reinterpret_cast<DeltaCol*>(d + o_cols);
     ctx->chainv = reinterpret_cast<ChainOp*>(d + o_chops);
+    int64_t cow_max = 0, fan_max = 0;
+    for (const CowArgs& a : cargs) {
+      cow_max = std::max(cow_max, (int64_t)a.c_out * a.fan_in * es);
+      fan_max = std::max(fan_max, a.fan_in);
+    }
     if (!cargs.empty())
-      HIPTRY(launch_cow(reinterpret_cast<const CowArgs*>(d + o_cargs), (int)cargs.size(),
+      HIPTRY(launch_cow(reinterpret_cast<const CowArgs*>(d + o_cargs), (int)cargs.size(), cow_max, fan_max,
                         reinterpret_cast<const DevRecord*>(d + o_drecs), reinterpret_cast<const float*>(d + o_noise),
                         g.dtype, st));
     HIPTRY(hipEventRecord(ctx->ev1, ctx->stream));
