@@ -308,7 +308,8 @@ mure_status mure_get_stats(const mure_ctx* ctx, mure_stats* out);
  *   "chunk_inputs"      inputs per chunk, multiple of 64 (0 = automatic)
  *   "fused_paths"       1 (default) fuse a residual block's ADD into its second
  *                       convolution and the kill into the output layer where
- *                       the graph allows; 0 run them as kernels of their own
+ *                       the graph allows, and run consecutive small bf16 nodes
+ *                       in one launch; 0 run them as kernels of their own
  *                       (the same results, bit for bit)
  *   "vanilla"           1: no memoization -- every mutant runs from the first
  *                       layer after the input (exhaustive mutation testing, the

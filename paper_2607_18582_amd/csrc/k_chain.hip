@@ -30,9 +30,9 @@
 // MFMA) and the vector instructions of the epilogues.
 //
 // Measured, layer by layer -> chains: run_mutants on ResNet-20, exhaustive,
-// 1,111 inputs x 61 mutants 24.2 -> 14.7 ms; ResNet-20, 2,500 x 200, 54.8 ->
-// 45.3 ms (259 -> 133 launches); MobileNetV2, 2,500 x 200, 59.3 -> 42.9 ms (704
-// -> 194 launches).
+// 1,111 inputs x 61 mutants 24.2 -> 14.7 ms (10.8 with the stem's own kernel);
+// ResNet-20, 2,500 x 200, 54.8 -> 43 ms (259 -> 133 launches); MobileNetV2,
+// 2,500 x 200, 59.3 -> 42.5 ms (704 -> 194 launches).
 #include "dev.hpp"
 
 namespace mure {
