@@ -788,7 +788,12 @@ void conv_halo_kernel(ConvArgs a) {
   halo_store_rows<W, TN, BM>(a, tl, rsh, 0, tid, Os, a.add_mode, skipv);
 }
 
-int conv_halo_bn(int cout) { return cout <= 32 ? 32 : 64; }
+// Columns per block: 64, or 32 for a node that has no more and where 64 give no
+// more blocks than CUs: a block's MFMAs halve while its staged input stays, and
+// the second block of the CU overlaps the first one's waits.
+static int conv_halo_bn(int ncol, int64_t bands, int nslots) {
+  return ncol <= 32 || bands * ((ncol + 63) / 64) * nslots <= 256 ? 32 : 64;
+}
 
 namespace {
 template <int W>
@@ -826,8 +831,8 @@ hipError_t launch_conv_halo(const ConvArgs& a0, int nslots, hipStream_t s) {
   if (a.cols) nslots = 1;
   const int TR = 512 / a.W;
   const int ncol = a.cols ? a.ncols : a.Cout;
-  const int bn = conv_halo_bn(ncol);
   const int64_t bands = ((int64_t)a.nx * a.H + TR - 1) / TR;
+  const int bn = conv_halo_bn(ncol, bands, nslots);
   const int zb = (ncol + bn - 1) / bn;
   const int64_t tiles = (bands + 7) / 8 * 8 * zb * nslots;
   if (tiles >= (1 << 30)) return hipErrorInvalidValue;

@@ -2,7 +2,8 @@
 width and image height the kernel's pixel layout distinguishes: with small
 integers every product and sum is exact, so the logits must equal a plain
 float32 reference bit for bit -- whole rows, pooled rows and an identity
-shortcut (its two-pass epilogue), and gathered columns of mutants."""
+shortcut (its two-pass epilogue), and gathered columns of mutants -- in
+launches of few blocks (32 columns each) and of more than one per CU (64)."""
 import numpy as np
 import pytest
 import torch
@@ -17,13 +18,16 @@ def bits(x):
     return torch.from_numpy(x.astype(np.float32)).bfloat16().view(torch.int16).numpy().view(np.uint16)
 
 
+@pytest.mark.parametrize("many", [False, True])
 @pytest.mark.parametrize("form", ["plain", "pool", "add"])
 @pytest.mark.parametrize("h,w,c,cout", [(8, 8, 16, 64), (16, 8, 32, 32), (32, 8, 16, 32), (64, 8, 16, 64),
                                         (16, 16, 48, 32), (32, 16, 16, 64), (16, 32, 16, 96), (48, 32, 32, 32),
                                         (8, 64, 16, 64), (64, 64, 16, 32)])
-def test_halo_conv_is_exact(h, w, c, cout, form):
+def test_halo_conv_is_exact(h, w, c, cout, form, many):
     rng = np.random.default_rng(5)
     n = 11 if h * w <= 512 else 3                        # several images a band, a ragged last one
+    if many:
+        n += 256 * 512 // (h * w)                        # more than 256 bands
     b = W.configs._Builder((h, w, c))
     if form == "add":
         cout = c if c % 32 == 0 else 32
