@@ -190,8 +190,9 @@ int node_family(const Graph& g, int v) {
 }
 
 // The ADD node that reads convolution v as its first input when nothing else
-// reads v (conv_b of a residual block): the pair runs as one launch whose
-// epilogue adds the shortcut.  -1 if v is not such a convolution.
+// reads v (conv_b of a residual block) and whose shortcut is an earlier node:
+// the pair runs as one launch whose epilogue adds the shortcut.  -1 if v is
+// not such a convolution.
 int fused_add_of(const Graph& g, int v) {
   const Node& n = g.nodes[v];
   const int fam = node_family(g, v);
@@ -201,6 +202,7 @@ int fused_add_of(const Graph& g, int v) {
     for (int k = 0; k < g.nodes[j].n_in; ++k)
       if (g.nodes[j].in[k] == v) { reader = j; ++count; }
   if (count != 1 || g.nodes[reader].kind != K_ADD || g.nodes[reader].in[0] != v) return -1;
+  if (g.nodes[reader].in[1] > v) return -1;              // the shortcut is computed after v
   if (fam == FAM_HALO && reader == g.out()) return -1;   // the halo kernel stores bf16 only
   return reader;
 }

@@ -185,7 +185,7 @@ struct Plan {
 void virtual_map(const Graph& g, const Plan& p, Group& gr);
 
 // The ADD node fused into convolution v's epilogue (v's only reader, reading
-// it as in[0]), or -1.
+// it as in[0], its shortcut an earlier node than v), or -1.
 int fused_add_of(const Graph& g, int v);
 
 // Memoization boundary K of a first mutated layer (Algorithm 1 / Section 4).
