@@ -15,6 +15,7 @@
 // (window q = py*Wp + px, then its 4 pixels), so the 4 accumulators a lane
 // holds for one output column are one pooling window.
 #include "dev.hpp"
+#include "plan.hpp"
 
 #include <algorithm>
 
@@ -199,7 +200,6 @@ __global__ __launch_bounds__(256) void conv_mfma_kernel(ConvArgs a) {
 // The scalar gather from global memory, with its index arithmetic per element,
 // had bound the stems: ResNet-20's over 67,771 images 4.16 -> 0.68 ms (3.3 TB/s
 // of input and output), the 43 gathered columns of the wide ResNet's 1.11 -> 0.74.
-constexpr int THIN_ROWS = 16;                            // output rows of a band, at most
 constexpr int THIN_LEAD = 8;                             // elements before a staged row's data (its left padding)
 
 template <int TN, bool COLS>
@@ -302,9 +302,10 @@ __global__ __launch_bounds__(256) void conv_thin_kernel(ConvArgs a, int band_row
 
 // Whether conv_thin_kernel computes a launch: one k step, rows of whole
 // 16-byte vectors (as the tensors' 256-byte aligned buffers then are), the
-// left padding within the staged rows' lead, and 8-byte output vectors.
+// left padding within the staged rows' lead, and 8-byte output vectors; and
+// enough pixels per block.
 static bool thin_fits(const ConvArgs& a, int dtype) {
-  return dtype == 1 && !a.pool && !a.add_mode && !a.out_f32 && !a.vin.chmap && a.K <= 32 && (a.W * a.C) % 8 == 0 &&
+  return dtype == 1 && conv_thin_pays(a.Hc, a.Wc, a.cols ? a.ncols : a.Cout, a.cols != nullptr, a.delta_T) && !a.pool && !a.add_mode && !a.out_f32 && !a.vin.chmap && a.K <= 32 && (a.W * a.C) % 8 == 0 &&
          a.in.row_elems == (int64_t)a.H * a.W * a.C && reinterpret_cast<uintptr_t>(a.in.p) % 16 == 0 &&
          reinterpret_cast<uintptr_t>(a.out) % 8 == 0 && a.pad * a.C <= THIN_LEAD && a.Cout % 4 == 0 &&
          a.out_row % 4 == 0 && a.Wc <= 1024 &&

@@ -106,6 +106,24 @@ inline bool lstm_wide_fits(int d, int h) {
 }
 int node_family(const Graph& g, int v);
 
+// Whether conv_thin_kernel, whose block is a band of THIN_ROWS output rows of
+// one image, beats the general kernel's 64 rows of any images.  Time of the
+// former over the latter's, by a block's pixels:
+//   whole layers: 64 pixels 0.6 with 16 columns, 0.75 with 32, 0.9 with 48, 1.2
+//     with 64; 96 pixels 0.45, 0.5, 0.6, 0.86; 256 pixels 0.3 to 0.55; 32 pixels
+//     and less 1.0 to 2.7, and 86 on a DENSE layer 32 -> 512 (one pixel a
+//     block; 10,000 inputs x 100 mutants 1.3 -> 111 ms);
+//   gathered columns, compact rows: 64 pixels 0.6 with 4 columns, 0.8 with 12,
+//     1.3 to 1.4 with more; 128 pixels 0.45, 0.6, 1.0; 256 pixels 0.3 to 0.88;
+//   gathered columns into whole rows (two bytes a store, one image at a
+//     time): 1.6 at 16 channels, 1.0 to 1.4 at 64.
+constexpr int THIN_ROWS = 16;
+inline bool conv_thin_pays(int Hc, int Wc, int ncol, bool cols, int delta_T) {
+  const int bands = (Hc + THIN_ROWS - 1) / THIN_ROWS, px = (int)((int64_t)Hc * Wc / bands);
+  if (cols) return delta_T > 0 && px >= (ncol <= 32 ? 64 : 128);
+  return px >= (ncol <= 48 ? 64 : 96);
+}
+
 // Launch geometry shared by the planner (family choice) and the kernels.
 // VALU convolution: rows per block and LDS bytes (zero-padded fp32 images of
 // those rows + the fp32 weights of every output channel).

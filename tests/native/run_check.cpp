@@ -2,7 +2,8 @@
 // UndefinedBehaviorSanitizer by tests/test_run_plan.py: over seeded random
 // bf16 graphs whose residual blocks list the shortcut's projection before or
 // after the main branch, a convolution is fused with its ADD only where the
-// shortcut is computed before the convolution.
+// shortcut is computed before the convolution; and the thin convolution kernel
+// is chosen where its blocks have enough pixels.
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -113,11 +114,25 @@ void check(const Build& b, int id) {
       printf("graph %d: convolution %d adds node %d, computed after it\n", id, v, g.nodes[fa].in[1]);
   }
 }
+
+// (output height, width, columns, gathered, compact channels, chosen)
+void check_thin() {
+  const int t[][6] = {{32, 32, 16, 0, 0, 1}, {32, 32, 64, 0, 0, 1}, {8, 8, 48, 0, 0, 1},  {8, 8, 64, 0, 0, 0},
+                      {12, 8, 64, 0, 0, 1},  {17, 8, 64, 0, 0, 0},  {17, 8, 32, 0, 0, 1}, {4, 8, 16, 0, 0, 0},
+                      {1, 1, 512, 0, 0, 0},  {1, 1, 16, 0, 0, 0},   {8, 8, 12, 1, 2, 1},  {8, 8, 40, 1, 2, 0},
+                      {16, 8, 40, 1, 2, 1},  {64, 64, 43, 1, 9, 1}, {64, 64, 43, 1, 0, 0}};
+  for (const auto& c : t)
+    if (conv_thin_pays(c[0], c[1], c[2], c[3] != 0, c[4]) != (c[5] != 0)) {
+      printf("thin convolution of %d x %d, %d columns: wrong kernel\n", c[0], c[1], c[2]);
+      ++failures;
+    }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
   const int n = argc > 1 ? atoi(argv[1]) : 200;
   Rng r{77};
+  check_thin();
   for (int i = 0; i < n; ++i) check(random_graph(r), i);
   printf("pairs %lld, failures %lld\n", (long long)pairs, (long long)failures);
   return failures != 0;

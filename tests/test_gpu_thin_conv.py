@@ -18,10 +18,13 @@ def bits(x):
 
 # (H, W, C, C_out, k, stride, pad): one band and several, ragged bands and
 # tiles, odd rows, one to eight channels of left padding, 1 to 100 outputs of 16
-# and 64 columns; the last two keep the general kernel (K > 32; W C % 8 != 0)
+# and 64 columns; planes on both sides of the size below which the general
+# kernel runs; the last two keep the general kernel too (K > 32; W C % 8 != 0)
 @pytest.mark.parametrize("shape", [(32, 32, 3, 16, 3, 1, 1), (17, 16, 3, 20, 3, 2, 1), (9, 8, 1, 4, 5, 1, 2),
                                    (12, 8, 2, 64, 4, 2, 0), (40, 24, 3, 100, 3, 1, 0), (5, 8, 4, 24, 2, 1, 2),
-                                   (33, 1, 8, 32, 1, 1, 0), (16, 16, 4, 16, 3, 1, 1), (10, 10, 3, 16, 3, 1, 1)])
+                                   (8, 8, 3, 48, 3, 1, 1), (8, 8, 3, 64, 3, 1, 1), (12, 8, 3, 64, 3, 1, 1),
+                                   (18, 8, 4, 24, 2, 1, 2), (66, 8, 8, 32, 1, 1, 0), (17, 8, 3, 64, 3, 1, 1),
+                                   (1, 1, 32, 512, 1, 1, 0), (33, 1, 8, 32, 1, 1, 0), (16, 16, 4, 16, 3, 1, 1), (10, 10, 3, 16, 3, 1, 1)])
 def test_thin_conv_is_exact(shape):
     h, w, c, cout, k, stride, pad = shape
     rng = np.random.default_rng(3)
