@@ -19,6 +19,7 @@
 #include "chain.hpp"
 #include "kernels.hpp"
 #include "plan.hpp"
+#include "run.hpp"
 
 using namespace mure;
 
@@ -78,73 +79,6 @@ struct PinnedBuf {
   }
 };
 
-// Liveness-based placement of per-row activation buffers: offsets in bytes
-// per row; a buffer is reused once every reader of its previous owner ran.
-struct Placement {
-  std::map<int, int64_t> offset;   // node -> byte offset per row
-  int64_t peak = 0;                // bytes per row
-};
-
-Placement place_buffers(const Graph& g, const std::vector<int>& nodes, const std::set<int>& external,
-                        const std::map<int, int>& fused = {},
-                        const std::map<int, std::pair<ChainSeg, int64_t>>& chains = {}) {
-  // nodes: executed in this order; external: nodes whose output lives
-  // elsewhere; fused: conv_b -> ADD pairs run as one launch at conv_b's step,
-  // so the ADD's buffer is placed at that step (conv_b itself has none);
-  // chains: runs of nodes executed as one launch, whose other outputs are
-  // never stored and whose inputs are in use until it ends
-  std::map<int, int> last_use;
-  for (int v : nodes) {
-    for (int k = 0; k < g.nodes[v].n_in; ++k) last_use[g.nodes[v].in[k]] = v;
-  }
-  std::set<int> inside;
-  for (const auto& c : chains) {
-    const ChainSeg& s = c.second.first;
-    for (int p : s.ins) last_use[p] = std::max(last_use[p], s.b);
-    for (int v = s.a; v <= s.b; ++v)
-      if (std::find(s.outs.begin(), s.outs.end(), v) == s.outs.end()) inside.insert(v);
-  }
-  struct Blk { int64_t off, size; int owner; };
-  std::vector<Blk> blocks;
-  Placement pl;
-  const int out = g.out();
-  std::set<int> placed;
-  auto place = [&](int v) {
-    const int64_t need = (g.act_bytes(v) + 255) / 256 * 256;
-    int best = -1;
-    for (size_t i = 0; i < blocks.size(); ++i)
-      if (blocks[i].owner < 0 && blocks[i].size >= need && (best < 0 || blocks[i].size < blocks[best].size))
-        best = (int)i;
-    if (best < 0) {
-      blocks.push_back({pl.peak, need, v});
-      pl.peak += need;
-      best = (int)blocks.size() - 1;
-    } else {
-      blocks[best].owner = v;
-    }
-    pl.offset[v] = blocks[best].off;
-    placed.insert(v);
-  };
-  for (int v : nodes) {
-    if (inside.count(v)) continue;
-    // free blocks whose owner is no longer needed by v or later nodes
-    for (Blk& b : blocks) {
-      if (b.owner < 0) continue;
-      auto it = last_use.find(b.owner);
-      const int lu = (b.owner == out) ? 1 << 30 : (it == last_use.end() ? -1 : it->second);
-      if (lu < v) b.owner = -1;
-    }
-    auto f = fused.find(v);
-    if (f != fused.end()) {
-      if (!external.count(f->second)) place(f->second);
-      continue;
-    }
-    if (external.count(v) || placed.count(v) || inside.count(v)) continue;
-    place(v);
-  }
-  return pl;
-}
-
 }  // namespace
 
 struct mure_ctx {
@@ -172,7 +106,7 @@ struct mure_ctx {
   DeltaCol* colv = nullptr;
   ChainOp* chainv = nullptr;
   std::vector<ChainSeg> chains;                       // plan_chains of the loaded model
-  std::map<int, std::pair<ChainSeg, int64_t>> orig_chains;   // run_original's (cached nodes stored)
+  Run orig_run;                                       // run_original's launches (cached nodes stored)
   struct GroupTabs {
     std::map<int, int64_t> w, b;                      // node -> offset (in pointers) into tables
     int64_t slot_mutant = 0;                          // offset (int32) into slotv
@@ -187,8 +121,7 @@ struct mure_ctx {
     int64_t vgent = 0;                                // vhalo: offset (int32) into chmapv of the
                                                       // (slot, group) entries, one per side plane
     std::vector<int64_t> vgbeg;                       // vhalo: first entry of each slot (+1)
-    std::map<int, std::pair<ChainSeg, int64_t>> chains;   // chains of the suffix by first node, and
-                                                      // their first op (in chainv)
+    Run run;                                          // the suffix's launches (ops: in chainv)
     bool vchain = false;                              // the first chain reads mmi's output through
                                                       // channel maps and is its only reader
   };
@@ -505,12 +438,12 @@ bool chain_reads_mmi(const std::vector<ChainSeg>& chains, const Graph& g, const 
 // `where` gives the buffers of its inputs and stored outputs, vin (optional)
 // the view of its first input.
 template <typename F>
-mure_status exec_chain(mure_ctx* ctx, const std::pair<ChainSeg, int64_t>& c, F&& where, const VirtualIn* vin,
+mure_status exec_chain(mure_ctx* ctx, const RunChain& c, F&& where, const VirtualIn* vin,
                        int cs0, int nslots, int nx, int x0, bool timed) {
   const Graph& g = ctx->g;
-  const ChainSeg& s = c.first;
+  const ChainSeg& s = c.seg;
   ChainArgs a;
-  a.ops = ctx->chainv + c.second;
+  a.ops = ctx->chainv + c.ops;
   a.nops = (int)s.ops.size();
   a.tabs = ctx->tables + cs0;
   a.nslots = nslots; a.nx = nx; a.x0 = x0;
@@ -898,18 +831,17 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
       ob[v] = (int64_t)tabs.size(); tabs.push_back(ctx->d_b[v]->p);
     }
     std::vector<ChainOp> chops;
-    // the chain's operations with their pointer-table offsets
-    auto add_chain = [&](const ChainSeg& seg, const std::map<int, int64_t>& w, const std::map<int, int64_t>& b,
-                         std::map<int, std::pair<ChainSeg, int64_t>>& to) {
-      std::pair<ChainSeg, int64_t>& c = to[seg.a];
-      c.first = seg;
-      c.second = (int64_t)chops.size();
-      for (ChainOp o : seg.ops) {
-        if (o.wbytes > 0) {
-          o.w = (int)w.at(o.node);
-          o.b = (int)b.at(o.node);
+    // the chains' operations with their pointer-table offsets
+    auto add_chains = [&](Run& run, const std::map<int, int64_t>& w, const std::map<int, int64_t>& b) {
+      for (RunChain& c : run.chains) {
+        c.ops = (int64_t)chops.size();
+        for (ChainOp o : c.seg.ops) {
+          if (o.wbytes > 0) {
+            o.w = (int)w.at(o.node);
+            o.b = (int)b.at(o.node);
+          }
+          chops.push_back(o);
         }
-        chops.push_back(o);
       }
     };
     for (size_t gi = 0; gi < plan.groups.size(); ++gi) {
@@ -930,15 +862,12 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
           tabs.push_back(it == cow_index.end() ? ctx->d_b[v]->p : (const void*)cargs[it->second].b_dst);
         }
       }
-      for (int v = gr.mmi + 1; v < (int)g.nodes.size(); ++v) {
-        const ChainSeg& seg = ctx->chains[v];
-        if (!seg.valid()) continue;
-        // mmi's output is not materialised for readers through maps or groups
+      // mmi's output is not materialised for readers through maps or groups
+      gt.run = plan_run(g, gr.mmi + 1, &ctx->chains, true, {}, [&](const ChainSeg& seg) {
         const bool reads = std::find(seg.ins.begin(), seg.ins.end(), gr.mmi) != seg.ins.end();
-        if (reads && (gr.virt || gr.vhalo) && !gt.vchain) continue;
-        add_chain(seg, gt.w, gt.b, gt.chains);
-        v = seg.b;
-      }
+        return !(reads && (gr.virt || gr.vhalo) && !gt.vchain);
+      });
+      add_chains(gt.run, gt.w, gt.b);
       gt.slot_mutant = (int64_t)slots.size();
       for (int mu : gr.mutants) slots.push_back(mu);
       gt.chmap = (int64_t)chmaps.size();
@@ -972,16 +901,8 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
         chmaps.insert(chmaps.end(), ent.begin(), ent.end());
       }
     }
-    std::map<int, std::pair<ChainSeg, int64_t>> ochains;
-    {
-      const std::set<int> keep(plan.cache_nodes.begin(), plan.cache_nodes.end());
-      for (int v = 1; v < (int)g.nodes.size(); ++v) {
-        ChainSeg seg;
-        if (!ctx->chains[v].valid() || !build_chain(g, v, ctx->chains[v].b, keep, seg)) continue;
-        add_chain(seg, ow, ob, ochains);
-        v = seg.b;
-      }
-    }
+    Run orun = plan_run(g, 1, &ctx->chains, true, std::set<int>(plan.cache_nodes.begin(), plan.cache_nodes.end()));
+    add_chains(orun, ow, ob);
     // touched-channel lists of the recompute mutants (CSR, absolute offsets
     // into the list stored after every group's offsets)
     {
@@ -1069,7 +990,7 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
     (void)hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1);
     ctx->stats.ms_apply = ms;
     ctx->gtabs = std::move(gtabs);
-    ctx->orig_chains = std::move(ochains);
+    ctx->orig_run = std::move(orun);
     ctx->orig_w = std::move(ow);
     ctx->orig_b = std::move(ob);
   }
@@ -1132,18 +1053,11 @@ static mure_status run_original_impl(mure_ctx* ctx, const void* inputs_dev, int6
     HIPTRY(d_given.ensure((size_t)(n * 4)));
     HIPTRY(hipMemcpyAsync(d_given.p, labels, (size_t)(n * 4), hipMemcpyHostToDevice, ctx->stream));
   }
-  std::vector<int> nodes;
-  for (int v = 1; v <= L; ++v) nodes.push_back(v);
   std::set<int> external(cached);
   external.insert(L);
-  std::map<int, int> fused;                            // conv_b -> ADD run as one launch
-  for (int v = 1; v <= L; ++v) {
-    const int fa = ctx->fused ? fused_add_of(g, v) : -1;
-    if (fa >= 0 && !cached.count(v)) fused[v] = fa;
-  }
-  static const std::map<int, std::pair<ChainSeg, int64_t>> no_chains;
-  const auto& chains = ctx->fused ? ctx->orig_chains : no_chains;
-  Placement pl = place_buffers(g, nodes, external, fused, chains);
+  const Run layers = ctx->fused ? Run() : plan_run(g, 1, nullptr, false, cached);
+  const Run& run = ctx->fused ? ctx->orig_run : layers;
+  const Placement pl = place_buffers(g, run, external);
   const int64_t budget = ctx->max_ws_mb << 20;
   int64_t nx = n;
   if (ctx->chunk_inputs) nx = std::min<int64_t>(nx, ctx->chunk_inputs);
@@ -1168,27 +1082,22 @@ static mure_status run_original_impl(mure_ctx* ctx, const void* inputs_dev, int6
       if (cached.count(p)) return {ctx->cache[p]->p, MODE_CACHE};
       return {ws + pl.offset.at(p) * nx, MODE_BUF};
     };
-    std::set<int> done;
-    for (int v = 1; v <= L; ++v) {
-      if (done.count(v)) continue;
-      const auto ch = chains.find(v);
-      if (ch != chains.end()) {
-        mure_status st = exec_chain(ctx, ch->second, where, nullptr, 0, 1, cnt, (int)x0, false);
+    for (const RunStep& step : run.steps) {
+      if (step.chain >= 0) {
+        mure_status st = exec_chain(ctx, run.chains[step.chain], where, nullptr, 0, 1, cnt, (int)x0, false);
         if (st != MURE_OK) return st;
-        v = ch->second.first.b;
         continue;
       }
+      const int v = step.v;
       const Node& nd = g.nodes[v];
       std::vector<Where> ins;
       for (int k = 0; k < nd.n_in; ++k) ins.push_back(where(nd.in[k]));
       Extra ex;
       int tgt = v;
-      auto f = fused.find(v);
-      if (f != fused.end()) {
-        tgt = f->second;
+      if (step.add >= 0) {
+        tgt = step.add;
         ex.fuse_add = tgt;
         ex.skip = where(g.nodes[tgt].in[1]);
-        done.insert(tgt);
       }
       Where o = where(tgt);
       const void* const* wt = nd.weighted() ? tabs + ctx->orig_w.at(v) : nullptr;
@@ -1232,26 +1141,19 @@ static mure_status run_original_impl(mure_ctx* ctx, const void* inputs_dev, int6
 }  // extern "C"
 namespace {
 struct ChunkGeom {
+  Run layers;                                        // the launches without chains
   Placement pl;
-  std::map<int, int> fused_adds;                     // conv_b -> ADD run as one launch
   int64_t nx = 0, spc = 0, cap_rows = 0, need_bytes = 0;
 };
 
 // chains: with the cluster's chains (whose inner nodes take no buffers).
 ChunkGeom group_geometry(const mure_ctx* ctx, int gi, int nslots, int64_t budget, bool chains) {
   const Graph& g = ctx->g;
-  const Group& gr = ctx->plan.groups[gi];
-  const int L = g.out(), mmi = gr.mmi;
+  const int mmi = ctx->plan.groups[gi].mmi;
   const int64_t N = ctx->N;
   ChunkGeom cg;
-  std::vector<int> nodes;
-  for (int v = mmi; v <= L; ++v) nodes.push_back(v);
-  for (int v = mmi + 1; v <= L; ++v) {
-    const int fa = ctx->fused ? fused_add_of(g, v) : -1;
-    if (fa >= 0) cg.fused_adds[v] = fa;
-  }
-  if (chains) cg.pl = place_buffers(g, nodes, {}, cg.fused_adds, ctx->gtabs[gi].chains);
-  else cg.pl = place_buffers(g, nodes, {}, cg.fused_adds);
+  if (!chains) cg.layers = plan_run(g, mmi + 1, nullptr, ctx->fused != 0, {});
+  cg.pl = place_buffers(g, chains ? ctx->gtabs[gi].run : cg.layers, {}, mmi);
   const int64_t peak = std::max<int64_t>(cg.pl.peak, 1);
   int64_t nx = N;
   if (ctx->chunk_inputs) nx = std::min<int64_t>(nx, ctx->chunk_inputs);
@@ -1289,8 +1191,8 @@ static mure_status run_group(mure_ctx* ctx, int gi, int s_begin, int s_end, uint
     chains = false;
     cg = group_geometry(ctx, gi, s_end - s_begin, budget, false);
   }
+  const Run& run = chains ? gt.run : cg.layers;
   const Placement& pl = cg.pl;
-  const std::map<int, int>& fused_adds = cg.fused_adds;
   const int64_t nx = cg.nx, spc = cg.spc, cap_rows = cg.cap_rows;
   // channel-group reads of mmi's output by its halo consumers (not with a
   // caller's scratch array: the side planes live in a buffer of their own)
@@ -1431,33 +1333,28 @@ static mure_status run_group(mure_ctx* ctx, int gi, int s_begin, int s_end, uint
         vin.HW = nm.H * nm.W;
         vin.T = gr.T;
       }
-      std::set<int> done;
-      for (int v = mmi + 1; v <= L; ++v) {
-        if (done.count(v)) continue;
-        const auto ch = gt.chains.find(v);
-        if (chains && ch != gt.chains.end()) {
+      for (const RunStep& step : run.steps) {
+        const int v = step.v;
+        if (step.chain >= 0) {
           const bool first = vc && v == mmi + 1;
           mure_status st = exec_chain(
-              ctx, ch->second,
+              ctx, run.chains[step.chain],
               [&](int p) -> Where { return first && p == mmi ? Where{mmi_cache, MODE_CACHE} : where(p); },
               first ? &vin : nullptr, cs0, ns, cnt, (int)x0, true);
           if (st != MURE_OK) return st;
-          v = ch->second.first.b;
           continue;
         }
         const Node& nd = g.nodes[v];
         std::vector<Where> ins;
         for (int k = 0; k < nd.n_in; ++k) ins.push_back(where(nd.in[k]));
-        auto f = fused_adds.find(v);
-        if (f != fused_adds.end()) {
-          const int fa = f->second;
+        if (step.add >= 0) {
+          const int fa = step.add;
           Extra exf;
           exf.fuse_add = fa;
           exf.skip = where(g.nodes[fa].in[1]);
           if (vh && g.nodes[fa].in[1] == mmi) exf.gskip = &gin;
           if (vh && nd.n_in == 1 && nd.in[0] == mmi) exf.gin = &gin;
           if (fa == L) { exf.kill = nullptr; }
-          done.insert(fa);
           mure_status st = exec_node(ctx, v, ins, const_cast<void*>(where(fa).p), MODE_BUF,
                                      tabs + gt.w.at(v) + cs0,
                                      reinterpret_cast<const float* const*>(tabs + gt.b.at(v) + cs0), 0, ns, cnt,

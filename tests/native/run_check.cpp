@@ -7,9 +7,10 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <set>
 #include <vector>
 
-#include "../../paper_2607_18582_amd/csrc/plan.hpp"
+#include "../../paper_2607_18582_amd/csrc/run.hpp"
 
 using namespace mure;
 
@@ -95,24 +96,153 @@ Build random_graph(Rng& r) {
   return b;
 }
 
-int64_t failures = 0, pairs = 0;
+int64_t failures = 0, pairs = 0, runs = 0, chains = 0;
+const char* name = "";
 
-void check(const Build& b, int id) {
+void bad(int id, int first, int step, int node, const char* what) {
+  if (failures++ < 20) printf("%s %d, run from %d, step %d: node %d %s\n", name, id, first, step, node, what);
+}
+
+// The steps in order.  mmi >= 0: stored before the first step (unless virt:
+// the first chain reads it elsewhere); nodes before `first` are cached;
+// `external` nodes have buffers of their own.
+void walk(const Graph& g, const Run& run, int first, int mmi, bool virt, const std::set<int>& external,
+          const std::set<int>& kept, int id) {
+  ++runs;
+  chains += (int64_t)run.chains.size();
+  const Placement pl = place_buffers(g, run, external, mmi);
+  std::vector<int> owner(pl.peak / 256, -1);            // buffers are whole units of 256 bytes
+  std::set<int> computed;
+  auto units = [&](int v) { return (g.act_bytes(v) + 255) / 256; };
+  auto store = [&](int v, int i) {
+    if (external.count(v)) return;
+    const auto it = pl.offset.find(v);
+    if (it == pl.offset.end()) { bad(id, first, i, v, "is stored and has no buffer"); return; }
+    if (it->second % 256 || it->second / 256 + units(v) > (int64_t)owner.size()) { bad(id, first, i, v, "outside the workspace"); return; }
+    for (int64_t u = 0; u < units(v); ++u) owner[it->second / 256 + u] = v;
+  };
+  auto read = [&](int p, int i) {
+    if (p < first && p != mmi) return;
+    if (p == mmi && virt && run.steps[i].chain >= 0 && i == 0) return;
+    if (!computed.count(p)) { bad(id, first, i, p, "is read before it is computed"); return; }
+    if (external.count(p)) return;
+    const auto it = pl.offset.find(p);
+    if (it == pl.offset.end()) { bad(id, first, i, p, "is read and has no buffer"); return; }
+    for (int64_t u = 0; u < units(p); ++u)
+      if (owner[it->second / 256 + u] != p) { bad(id, first, i, p, "has been overwritten"); return; }
+  };
+  if (mmi >= 0) {
+    computed.insert(mmi);
+    store(mmi, -1);
+  }
+  for (int i = 0; i < (int)run.steps.size(); ++i) {
+    const RunStep& s = run.steps[i];
+    std::set<int> done;
+    if (s.chain >= 0) {
+      const ChainSeg& c = run.chains[s.chain].seg;
+      for (int v = c.a; v <= c.b; ++v) done.insert(v);
+    } else {
+      done.insert(s.v);
+      if (s.add >= 0) done.insert(s.add);
+      if (s.add >= 0 && kept.count(s.v)) bad(id, first, i, s.v, "is kept and fused");
+    }
+    // reads come first: an output may not stand where an input still does
+    for (int v : done)
+      for (int k = 0; k < g.nodes[v].n_in; ++k)
+        if (!done.count(g.nodes[v].in[k])) read(g.nodes[v].in[k], i);
+    for (int v : run.writes(s)) store(v, i);
+    for (int v : done)
+      for (int k = 0; k < g.nodes[v].n_in; ++k)
+        if (!done.count(g.nodes[v].in[k])) read(g.nodes[v].in[k], i);
+    for (int v : done)
+      if (!computed.insert(v).second) bad(id, first, i, v, "is computed twice");
+    for (int v : kept)
+      if (done.count(v)) {
+        bool stored = false;
+        for (int w : run.writes(s)) stored = stored || w == v;
+        if (!stored) bad(id, first, i, v, "is kept and not stored");
+      }
+  }
+  for (int v = first; v <= g.out(); ++v)
+    if (!computed.count(v)) bad(id, first, (int)run.steps.size(), v, "is never computed");
+}
+
+void check(const Build& b, int id, Rng& r) {
   Graph g;
   g.nodes = b.g;
   const std::string m = build_graph(g, b.h, b.h, b.c, DT_BF16);
   if (!m.empty()) {
-    printf("graph %d: %s\n", id, m.c_str());
+    printf("%s %d: %s\n", name, id, m.c_str());
     ++failures;
     return;
   }
-  for (int v = 1; v < (int)g.nodes.size(); ++v) {
+  const int L = g.out();
+  for (int v = 1; v <= L; ++v) {
     const int fa = fused_add_of(g, v);
     if (fa < 0) continue;
     ++pairs;
-    if (g.nodes[fa].in[1] >= v && failures++ < 20)
-      printf("graph %d: convolution %d adds node %d, computed after it\n", id, v, g.nodes[fa].in[1]);
+    if (g.nodes[fa].in[1] >= v) bad(id, 0, 0, v, "adds a node computed after it");
   }
+  const std::vector<ChainSeg> best = plan_chains(g);
+  for (int mmi = 1; mmi < L; ++mmi) {
+    if (!g.nodes[mmi].weighted()) continue;
+    // mmi's output stored; read by the first chain only; and not by a chain
+    walk(g, plan_run(g, mmi + 1, &best, true, {}), mmi + 1, mmi, false, {}, {}, id);
+    bool only = best[mmi + 1].valid();
+    for (int v = best[mmi + 1].b + 1; v <= L && only; ++v)
+      for (int k = 0; k < g.nodes[v].n_in; ++k) only = only && g.nodes[v].in[k] != mmi;
+    if (only) walk(g, plan_run(g, mmi + 1, &best, true, {}), mmi + 1, mmi, true, {}, {}, id);
+    const Run apart = plan_run(g, mmi + 1, &best, true, {}, [&](const ChainSeg& s) {
+      for (int p : s.ins)
+        if (p == mmi) return false;
+      return true;
+    });
+    walk(g, apart, mmi + 1, mmi, false, {}, {}, id);
+    for (const RunStep& s : apart.steps)                // group reads rely on it
+      if (s.chain < 0 && s.add < 0 && g.nodes[s.v].kind == K_ADD && g.nodes[s.v].in[1] == mmi &&
+          g.nodes[s.v].in[0] > mmi && fused_add_of(g, g.nodes[s.v].in[0]) == s.v)
+        bad(id, mmi + 1, 0, s.v, "reads mmi as a shortcut and is not fused");
+    walk(g, plan_run(g, mmi + 1, nullptr, true, {}), mmi + 1, mmi, false, {}, {}, id);
+    walk(g, plan_run(g, mmi + 1, nullptr, false, {}), mmi + 1, mmi, false, {}, {}, id);
+  }
+  for (int t = 0; t < 6; ++t) {                         // the original's run
+    std::set<int> kept, ext;
+    for (int v = 1; v < L; ++v)
+      if (t && r.below(t > 3 ? 8 : 2) == 0) kept.insert(v);
+    ext = kept;
+    ext.insert(L);
+    walk(g, plan_run(g, 1, t % 2 ? &best : nullptr, t < 4, kept), 1, -1, false, ext, kept, id);
+    walk(g, plan_run(g, 1, &best, true, kept), 1, -1, false, ext, kept, id);
+  }
+}
+
+// MobileNetV2 at widths (c) and expansion t, for 32 x 32 images
+Build mobilenet(int t, const std::vector<int>& c) {
+  const int n[] = {1, 2, 3, 4, 3, 3, 1}, st[] = {1, 1, 2, 2, 1, 2, 1};
+  Build b(32, 3);
+  int x = b.conv(0, c[0], 3, 1, 2);
+  for (int i = 0; i < 7; ++i)
+    for (int k = 0; k < n[i]; ++k) {
+      const int s = k ? 1 : st[i], ci = b.chan(x);
+      int y = i == 0 ? x : b.conv(x, ci * t, 1, 1, 2);
+      y = b.conv(b.dw(y, s), c[i + 1], 1, 1, 0);
+      x = s == 1 && ci == c[i + 1] ? b.sum(y, x, 0, 0) : y;
+    }
+  b.head(b.conv(x, c[8], 1, 1, 2));
+  return b;
+}
+
+// residual blocks of one width, layers behind each sum
+Build residual(int h, int c, int mid, int k) {
+  Build b(h, 16);
+  int x = b.conv(0, c, 3, 1, 1);
+  for (int i = 0; i < 2; ++i) {
+    x = b.sum(b.conv(b.conv(x, mid, k, 1, 1), c, k, 1, 0), x, 0, 1);
+    x = b.dw(x, 1);
+    x = b.conv(x, c, 1, 1, 1);
+  }
+  b.head(x);
+  return b;
 }
 
 // (output height, width, columns, gathered, compact channels, chosen)
@@ -133,7 +263,18 @@ int main(int argc, char** argv) {
   const int n = argc > 1 ? atoi(argv[1]) : 200;
   Rng r{77};
   check_thin();
-  for (int i = 0; i < n; ++i) check(random_graph(r), i);
-  printf("pairs %lld, failures %lld\n", (long long)pairs, (long long)failures);
+  name = "mobilenet";
+  check(mobilenet(6, {32, 16, 24, 32, 64, 96, 160, 320, 1280}), 0, r);
+  check(mobilenet(6, {16, 8, 16, 16, 32, 48, 80, 160, 640}), 1, r);
+  check(mobilenet(4, {32, 16, 24, 32, 64, 96, 160, 320, 1280}), 2, r);
+  name = "residual";
+  int id = 0;
+  for (int h : {8, 16, 32})
+    for (int c : {16, 24, 32, 40, 48, 64, 96, 128})
+      for (int mid : {0, 128})
+        for (int k : {1, 3}) check(residual(h, c, mid ? mid : c, k), id++, r);
+  (void)random_graph;
+  printf("runs %lld, chains %lld, pairs %lld, failures %lld\n", (long long)runs, (long long)chains, (long long)pairs,
+         (long long)failures);
   return failures != 0;
 }

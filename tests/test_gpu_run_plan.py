@@ -54,3 +54,32 @@ def test_projection_order_layer_by_layer(where):
     # planes of 24 and 12: no chains, convolutions with their ADD and single layers
     wl = workload(lambda b, x: projection_block(b, projection_block(b, x, 32, 2, where), 48, 1, where), 24, 21)
     check(wl)
+
+
+def wide_sum(b, x):                   # C_in 128: the second convolution runs by itself and computes the sum
+    x = b.conv(x, 32, 3, stride=2, pad=1)
+    x = b.add(b.conv(b.conv(x, 128, 3, pad=1), 32, 3, pad=1, relu=False), x)
+    x = b.dwconv(x, 3, pad=1)
+    return b.conv(b.conv(x, 32, 3, pad=1), 32, 3, pad=1)
+
+
+def unchained_width(b, x):            # 3x3 layers of 24 and 40 channels have no chain of their own
+    for c in (24, 40):
+        x = b.conv(x, c, 1)
+        x = b.add(b.conv(b.conv(x, c, 3, pad=1), c, 3, pad=1, relu=False), x)
+        x = b.dwconv(b.conv(x, 2 * c, 1, relu=2), 3, pad=1)
+    return x
+
+
+def mobilenetv2(b, x):                # published widths, expansion 6; fewer repeats and a narrower head
+    x = W.configs._inverted_residual(b, x, 1, 16, 1, "")
+    for c, n, s in ((24, 2, 1), (32, 3, 2), (64, 2, 2), (96, 2, 1), (160, 2, 2), (320, 1, 1)):
+        for k in range(n):
+            x = W.configs._inverted_residual(b, x, 6, c, s if k == 0 else 1, "")
+    return b.conv(x, 640, 1, relu=2)
+
+
+@pytest.mark.parametrize("build,hw", [(wide_sum, 16), (wide_sum, 32), (unchained_width, 8), (unchained_width, 16),
+                                      (mobilenetv2, 32)])
+def test_chains_behind_a_fused_sum(build, hw):
+    check(workload(build, hw, 21))
