@@ -273,7 +273,8 @@ int main(int argc, char** argv) {
     for (int c : {16, 24, 32, 40, 48, 64, 96, 128})
       for (int mid : {0, 128})
         for (int k : {1, 3}) check(residual(h, c, mid ? mid : c, k), id++, r);
-  (void)random_graph;
+  name = "random";
+  for (int i = 0; i < n; ++i) check(random_graph(r), i, r);
   printf("runs %lld, chains %lld, pairs %lld, failures %lld\n", (long long)runs, (long long)chains, (long long)pairs,
          (long long)failures);
   return failures != 0;
