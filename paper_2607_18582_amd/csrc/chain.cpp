@@ -71,35 +71,13 @@ bool chainable(const Graph& g, int v) {
   }
 }
 
-// What planning asks of every node, worked out once per graph.
-struct Info {
-  std::vector<int> fam, fused, readers, last;          // family, fused ADD, readers, last reader
-  std::vector<char> ok;                                // chainable
-  std::vector<std::vector<int>> convs;                 // convolutions reading the node
-  explicit Info(const Graph& g) {
-    const int n = (int)g.nodes.size();
-    fam.resize(n); fused.resize(n); readers.assign(n, 0); last.assign(n, -1); ok.resize(n); convs.resize(n);
-    for (int v = 0; v < n; ++v) {
-      const Node& nd = g.nodes[v];
-      fam[v] = node_family(g, v);
-      fused[v] = fused_add_of(g, v);
-      ok[v] = chainable(g, v);
-      for (int k = 0; k < nd.n_in; ++k) {
-        readers[nd.in[k]]++;
-        last[nd.in[k]] = v;
-      }
-      if (nd.kind == K_CONV || nd.kind == K_DWCONV) convs[nd.in[0]].push_back(v);
-    }
-  }
-};
-
 // LDS layout of node t's activation for its readers in [a, b].
 struct Layout {
   int bd = 0, pxb = 0, sh = 0, mask = 0;
   bool operator==(const Layout& o) const { return bd == o.bd && pxb == o.pxb && sh == o.sh && mask == o.mask; }
 };
 
-Layout layout_of(const Graph& g, const Info& f, int t, int a, int b) {
+Layout layout_of(const Graph& g, const ChainInfo& f, int t, int a, int b) {
   Layout l;
   bool halo = false, other = false;
   for (int v : f.convs[t]) {
@@ -159,7 +137,7 @@ ChainT tensor(const Layout& l, int off, int W) {
 
 // dry: the cost and the LDS only, no operations.  `slice`: output channels of an expansion convolution computed at a time for
 // the depthwise node after it (0: all).
-bool build_with_slice(const Graph& g, const Info& f, int a, int b, const std::set<int>& keep, int slice, bool dry, ChainSeg& s) {
+bool build_with_slice(const Graph& g, const ChainInfo& f, int a, int b, const std::set<int>& keep, int slice, bool dry, ChainSeg& s) {
   s = ChainSeg();
   s.a = a;
   const int N = b + 1;
@@ -382,7 +360,7 @@ bool build_with_slice(const Graph& g, const Info& f, int a, int b, const std::se
 
 namespace {
 // The cheapest way to slice the expansions of a .. b (-1: it does not fit).
-double cheapest(const Graph& g, const Info& f, int a, int b, const std::set<int>& keep, int& slice) {
+double cheapest(const Graph& g, const ChainInfo& f, int a, int b, const std::set<int>& keep, int& slice) {
   bool expands = false;
   for (int v = a; v < b; ++v) expands = expands || (g.nodes[v + 1].kind == K_DWCONV && g.nodes[v].kind == K_CONV);
   double best = -1;
@@ -400,17 +378,35 @@ double cheapest(const Graph& g, const Info& f, int a, int b, const std::set<int>
 }
 }  // namespace
 
-bool build_chain(const Graph& g, int a, int b, const std::set<int>& keep, ChainSeg& s) {
-  const Info f(g);
+ChainInfo::ChainInfo(const Graph& g) {
+  const int n = (int)g.nodes.size();
+  fam.resize(n); fused.resize(n); readers.assign(n, 0); last.assign(n, -1); ok.resize(n); convs.resize(n);
+  for (int v = 0; v < n; ++v) {
+    const Node& nd = g.nodes[v];
+    fam[v] = node_family(g, v);
+    fused[v] = fused_add_of(g, v);
+    ok[v] = chainable(g, v);
+    for (int k = 0; k < nd.n_in; ++k) {
+      readers[nd.in[k]]++;
+      last[nd.in[k]] = v;
+    }
+    if (nd.kind == K_CONV || nd.kind == K_DWCONV) convs[nd.in[0]].push_back(v);
+  }
+}
+
+bool build_chain(const Graph& g, const ChainInfo& f, int a, int b, const std::set<int>& keep, ChainSeg& s) {
   int slice = 0;
   return cheapest(g, f, a, b, keep, slice) >= 0 && build_with_slice(g, f, a, b, keep, slice, false, s);
 }
+bool build_chain(const Graph& g, int a, int b, const std::set<int>& keep, ChainSeg& s) {
+  return build_chain(g, ChainInfo(g), a, b, keep, s);
+}
 
-std::vector<ChainSeg> plan_chains(const Graph& g) {
+std::vector<ChainSeg> plan_chains(const Graph& g) { return plan_chains(g, ChainInfo(g)); }
+std::vector<ChainSeg> plan_chains(const Graph& g, const ChainInfo& f) {
   const int n = (int)g.nodes.size();
   std::vector<ChainSeg> best(n);
   if (g.dtype != DT_BF16) return best;
-  const Info f(g);
   std::vector<double> cost(n + 1, 0);
   std::vector<int> end(n, 0), sliced(n, 0);
   for (int v = n - 1; v >= 1; --v) {

@@ -30,9 +30,19 @@ struct ChainSeg {
 // its ADD.  false: some node cannot be in a chain, or it does not fit.
 bool build_chain(const Graph& g, int a, int b, const std::set<int>& keep, ChainSeg& s);
 
+// What planning asks of every node, worked out once per graph.
+struct ChainInfo {
+  std::vector<int> fam, fused, readers, last;          // family, fused ADD, readers, last reader
+  std::vector<char> ok;                                // can be in a chain
+  std::vector<std::vector<int>> convs;                 // convolutions reading the node
+  explicit ChainInfo(const Graph& g);
+};
+bool build_chain(const Graph& g, const ChainInfo& f, int a, int b, const std::set<int>& keep, ChainSeg& s);
+
 // For every node v the chain a suffix whose next node is v starts with
 // (invalid: v runs by itself), minimising the estimated cost of the whole
 // suffix.
 std::vector<ChainSeg> plan_chains(const Graph& g);
+std::vector<ChainSeg> plan_chains(const Graph& g, const ChainInfo& f);
 
 }  // namespace mure

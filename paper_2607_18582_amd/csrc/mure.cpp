@@ -105,7 +105,7 @@ struct mure_ctx {
   int32_t* chmapv = nullptr;
   DeltaCol* colv = nullptr;
   ChainOp* chainv = nullptr;
-  std::vector<ChainSeg> chains;                       // plan_chains of the loaded model
+  std::unique_ptr<Chains> chains;                     // of the loaded model
   Run orig_run;                                       // run_original's launches (cached nodes stored)
   struct GroupTabs {
     std::map<int, int64_t> w, b;                      // node -> offset (in pointers) into tables
@@ -665,7 +665,7 @@ static mure_status load_model_impl(mure_ctx* ctx, const mure_layer* layers, int3
     HIPTRY(hipStreamSynchronize(ctx->stream));
   }
   ctx->g = std::move(g);
-  ctx->chains = plan_chains(ctx->g);
+  ctx->chains.reset(new Chains(ctx->g));
   ctx->have_graph = true;
   ctx->plan = Plan();
   ctx->recs.clear();
@@ -847,7 +847,7 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
     for (size_t gi = 0; gi < plan.groups.size(); ++gi) {
       Group& gr = plan.groups[gi];
       mure_ctx::GroupTabs& gt = gtabs[gi];
-      gt.vchain = chain_reads_mmi(ctx->chains, g, gr);
+      gt.vchain = chain_reads_mmi(ctx->chains->best, g, gr);
       if (gt.vchain) virtual_map(g, plan, gr);
       for (int v = gr.mmi; v < (int)g.nodes.size(); ++v) {
         if (!g.nodes[v].weighted()) continue;
@@ -863,7 +863,7 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
         }
       }
       // mmi's output is not materialised for readers through maps or groups
-      gt.run = plan_run(g, gr.mmi + 1, &ctx->chains, true, {}, [&](const ChainSeg& seg) {
+      gt.run = plan_run(g, gr.mmi + 1, ctx->chains.get(), true, {}, [&](const ChainSeg& seg) {
         const bool reads = std::find(seg.ins.begin(), seg.ins.end(), gr.mmi) != seg.ins.end();
         return !(reads && (gr.virt || gr.vhalo) && !gt.vchain);
       });
@@ -901,7 +901,7 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
         chmaps.insert(chmaps.end(), ent.begin(), ent.end());
       }
     }
-    Run orun = plan_run(g, 1, &ctx->chains, true, std::set<int>(plan.cache_nodes.begin(), plan.cache_nodes.end()));
+    Run orun = plan_run(g, 1, ctx->chains.get(), true, std::set<int>(plan.cache_nodes.begin(), plan.cache_nodes.end()));
     add_chains(orun, ow, ob);
     // touched-channel lists of the recompute mutants (CSR, absolute offsets
     // into the list stored after every group's offsets)

@@ -18,7 +18,7 @@ std::vector<int> Run::writes(const RunStep& s) const {
   return {s.add >= 0 ? s.add : s.v};
 }
 
-Run plan_run(const Graph& g, int first, const std::vector<ChainSeg>* best, bool fuse, const std::set<int>& kept,
+Run plan_run(const Graph& g, int first, const Chains* chains, bool fuse, const std::set<int>& kept,
              const std::function<bool(const ChainSeg&)>& usable) {
   Run run;
   std::set<int> fused;                                 // ADDs computed by a convolution's launch
@@ -27,9 +27,11 @@ Run plan_run(const Graph& g, int first, const std::vector<ChainSeg>* best, bool 
     if (fused.count(v)) continue;
     RunStep s;
     s.v = v;
-    if (best && (*best)[v].valid() && (!usable || usable((*best)[v]))) {
-      ChainSeg seg;
-      if (build_chain(g, v, (*best)[v].b, kept, seg)) {
+    if (chains && chains->best[v].valid() && (!usable || usable(chains->best[v]))) {
+      // planned with nothing kept inside; a kept node changes its operations
+      ChainSeg seg = chains->best[v];
+      const auto k = kept.lower_bound(v);
+      if (k == kept.end() || *k > seg.b || build_chain(g, chains->info, v, seg.b, kept, seg)) {
         s.chain = (int)run.chains.size();
         v = seg.b;
         run.chains.push_back({std::move(seg), 0});

@@ -33,10 +33,18 @@ struct Run {
   std::vector<int> writes(const RunStep& s) const;                   // nodes it stores
 };
 
-// Nodes first .. out as steps.  best: plan_chains' chains (nullptr: none); a
-// chain is taken where usable, if given, accepts it.  fuse: convolutions
-// compute their ADD.  kept: nodes whose own output must be stored.
-Run plan_run(const Graph& g, int first, const std::vector<ChainSeg>* best, bool fuse, const std::set<int>& kept,
+// A graph's chains by their first node (plan_chains), and what plan_run needs
+// to build one that stores more of its nodes.
+struct Chains {
+  ChainInfo info;
+  std::vector<ChainSeg> best;
+  explicit Chains(const Graph& g) : info(g), best(plan_chains(g, info)) {}
+};
+
+// Nodes first .. out as steps.  chains: nullptr: none; a chain is taken where
+// usable, if given, accepts it.  fuse: convolutions compute their ADD.  kept:
+// nodes whose own output must be stored.
+Run plan_run(const Graph& g, int first, const Chains* chains, bool fuse, const std::set<int>& kept,
              const std::function<bool(const ChainSeg&)>& usable = {});
 
 // Liveness-based placement of per-row activation buffers: offsets in bytes

@@ -7,6 +7,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <set>
 #include <vector>
 
@@ -110,6 +111,13 @@ void walk(const Graph& g, const Run& run, int first, int mmi, bool virt, const s
           const std::set<int>& kept, int id) {
   ++runs;
   chains += (int64_t)run.chains.size();
+  for (const RunChain& c : run.chains) {                // as planned from the graph alone
+    ChainSeg s;
+    if (!build_chain(g, c.seg.a, c.seg.b, kept, s) || s.ops.size() != c.seg.ops.size() || s.ins != c.seg.ins ||
+        s.outs != c.seg.outs || s.arena != c.seg.arena || s.gmax != c.seg.gmax ||
+        memcmp(s.ops.data(), c.seg.ops.data(), s.ops.size() * sizeof(ChainOp)))
+      bad(id, first, 0, c.seg.a, "starts another chain than build_chain's");
+  }
   const Placement pl = place_buffers(g, run, external, mmi);
   std::vector<int> owner(pl.peak / 256, -1);            // buffers are whole units of 256 bytes
   std::set<int> computed;
@@ -183,16 +191,17 @@ void check(const Build& b, int id, Rng& r) {
     ++pairs;
     if (g.nodes[fa].in[1] >= v) bad(id, 0, 0, v, "adds a node computed after it");
   }
-  const std::vector<ChainSeg> best = plan_chains(g);
+  const Chains chains(g);
+  const std::vector<ChainSeg>& best = chains.best;
   for (int mmi = 1; mmi < L; ++mmi) {
     if (!g.nodes[mmi].weighted()) continue;
     // mmi's output stored; read by the first chain only; and not by a chain
-    walk(g, plan_run(g, mmi + 1, &best, true, {}), mmi + 1, mmi, false, {}, {}, id);
+    walk(g, plan_run(g, mmi + 1, &chains, true, {}), mmi + 1, mmi, false, {}, {}, id);
     bool only = best[mmi + 1].valid();
     for (int v = best[mmi + 1].b + 1; v <= L && only; ++v)
       for (int k = 0; k < g.nodes[v].n_in; ++k) only = only && g.nodes[v].in[k] != mmi;
-    if (only) walk(g, plan_run(g, mmi + 1, &best, true, {}), mmi + 1, mmi, true, {}, {}, id);
-    const Run apart = plan_run(g, mmi + 1, &best, true, {}, [&](const ChainSeg& s) {
+    if (only) walk(g, plan_run(g, mmi + 1, &chains, true, {}), mmi + 1, mmi, true, {}, {}, id);
+    const Run apart = plan_run(g, mmi + 1, &chains, true, {}, [&](const ChainSeg& s) {
       for (int p : s.ins)
         if (p == mmi) return false;
       return true;
@@ -211,8 +220,8 @@ void check(const Build& b, int id, Rng& r) {
       if (t && r.below(t > 3 ? 8 : 2) == 0) kept.insert(v);
     ext = kept;
     ext.insert(L);
-    walk(g, plan_run(g, 1, t % 2 ? &best : nullptr, t < 4, kept), 1, -1, false, ext, kept, id);
-    walk(g, plan_run(g, 1, &best, true, kept), 1, -1, false, ext, kept, id);
+    walk(g, plan_run(g, 1, t % 2 ? &chains : nullptr, t < 4, kept), 1, -1, false, ext, kept, id);
+    walk(g, plan_run(g, 1, &chains, true, kept), 1, -1, false, ext, kept, id);
   }
 }
 
