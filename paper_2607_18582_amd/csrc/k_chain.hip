@@ -35,6 +35,8 @@
 // 2,500 x 200, 59.3 -> 42.5 ms (704 -> 194 launches).
 #include "dev.hpp"
 
+#include <algorithm>
+
 namespace mure {
 
 namespace {
@@ -600,11 +602,9 @@ __device__ __forceinline__ void gap_rows(const Blk& k, const ChainOp& o, const C
 
 __global__ __launch_bounds__(NT, 4) void chain_kernel(ChainArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char chain_sm[];
-  // block b runs on XCD b % 8; each XCD takes a contiguous run of (slot,
-  // image group), so the blocks running together on it share their slot's
-  // weights in its L2
-  const int b = (int)blockIdx.x, idx = (b & 7) * a.turns + (b >> 3);
-  if (idx >= a.nslots * a.per_slot) return;             // padding of the order (whole block)
+  // the blocks running together on an XCD share their slot's weights in its L2
+  const int idx = chain_block((int)blockIdx.x, a.first, a.turns);
+  if (idx >= a.end) return;                             // padding of the order (whole block)
   Blk k;
   k.sm = chain_sm;
   k.G = a.G;
@@ -679,9 +679,17 @@ hipError_t launch_chain(const ChainArgs& a0, hipStream_t s) {
   a.per_slot = (a.nx + a.G - 1) / a.G;
   const int64_t blocks = (int64_t)a.per_slot * a.nslots;
   if (blocks >= (1 << 30)) return hipErrorInvalidValue;
-  a.turns = (int)((blocks + 7) / 8);
-  hipLaunchKernelGGL(chain_kernel, dim3((unsigned)(a.turns * 8)), dim3(NT), (size_t)(a.G * a.arena + CHAIN_EXTRA), s, a);
-  return hipGetLastError();
+  // a grid holds fewer than 2^32 threads: the blocks of large runs over several
+  // launches
+  for (int64_t b0 = 0; b0 < blocks; b0 += CHAIN_GRID) {
+    a.first = (int)b0;
+    a.end = (int)std::min<int64_t>(b0 + CHAIN_GRID, blocks);
+    a.turns = (a.end - a.first + 7) / 8;
+    hipLaunchKernelGGL(chain_kernel, dim3((unsigned)(a.turns * 8)), dim3(NT), (size_t)(a.G * a.arena + CHAIN_EXTRA), s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace mure

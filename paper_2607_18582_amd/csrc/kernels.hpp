@@ -334,7 +334,8 @@ struct ChainArgs {
   const void* const* tabs = nullptr;     // pointer tables, offset to the launch's first slot
   int nslots = 0, nx = 0, x0 = 0;
   int G = 1, arena = 0;                  // images per block, LDS bytes per image
-  int per_slot = 0, turns = 0;           // filled by the launcher: blocks per slot, blocks per XCD
+  int per_slot = 0, turns = 0, end = 0;  // filled by the launcher: blocks per slot; blocks per XCD
+  int first = 0;                         // of this launch, its first block and one past its last
   VirtualIn vin;                         // buffer 0 read through channel maps (vin.chmap set)
   ChainBuf buf[CHAIN_BUFS];
 };
@@ -344,6 +345,12 @@ constexpr int CHAIN_LIST = 64;              // changed channels of a virtual inp
 // LDS past the arenas: a zero slot, an unread slot, pointers, the list
 constexpr int CHAIN_EXTRA = 32 + 16 * CHAIN_OPS + 4 * (1 + 2 * CHAIN_LIST) + 12;
 constexpr int CHAIN_WAVES = 8;
+constexpr int CHAIN_GRID = 1 << 22;         // most blocks of a launch
+static_assert((int64_t)CHAIN_GRID * 64 * CHAIN_WAVES < ((int64_t)1 << 32), "a grid has fewer than 2^32 threads");
+// Block b of a launch of blocks [first, end): the block it stands for, or end
+// and more for the padding of the order.  Block b runs on XCD b % 8; each XCD
+// takes a contiguous run of `turns` blocks.
+__host__ __device__ inline int chain_block(int b, int first, int turns) { return first + (b & 7) * turns + (b >> 3); }
 
 // launchers (return the launch status)
 hipError_t launch_chain(const ChainArgs& a, hipStream_t s);

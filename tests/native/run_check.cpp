@@ -4,6 +4,7 @@
 // after the main branch, a convolution is fused with its ADD only where the
 // shortcut is computed before the convolution; and the thin convolution kernel
 // is chosen where its blocks have enough pixels.
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -266,12 +267,27 @@ void check_thin() {
       ++failures;
     }
 }
+// a chain's blocks over launches of CHAIN_GRID: each block once
+void check_grid() {
+  for (const int64_t blocks : {(int64_t)1, (int64_t)7, (int64_t)4097, (int64_t)CHAIN_GRID, (int64_t)CHAIN_GRID + 5}) {
+    std::vector<char> seen((size_t)blocks, 0);
+    for (int64_t b0 = 0; b0 < blocks; b0 += CHAIN_GRID) {
+      const int first = (int)b0, end = (int)std::min<int64_t>(b0 + CHAIN_GRID, blocks), turns = (end - first + 7) / 8;
+      for (int b = 0; b < turns * 8; ++b) {
+        const int idx = chain_block(b, first, turns);
+        if (idx < end && seen[(size_t)idx]++) ++failures;
+      }
+    }
+    for (char c : seen) failures += !c;
+  }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
   const int n = argc > 1 ? atoi(argv[1]) : 200;
   Rng r{77};
   check_thin();
+  check_grid();
   name = "mobilenet";
   check(mobilenet(6, {32, 16, 24, 32, 64, 96, 160, 320, 1280}), 0, r);
   check(mobilenet(6, {16, 8, 16, 16, 32, 48, 80, 160, 640}), 1, r);
