@@ -1,6 +1,6 @@
 """The wide LSTM kernel with 64 and with 16 rows per block gives the same
-values: a run of many mutants takes the one, a single mutant's logits the
-other (lstm_wide_rows)."""
+logits, bit for bit: a launch over 16,384 inputs of one model takes the one, a
+launch over about 1,000 the other (lstm_wide_rows)."""
 import numpy as np
 import pytest
 
@@ -11,14 +11,21 @@ from paper_2607_18582_amd import Mure
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n", [1000, 961])               # whole blocks of 16 and 64 rows; one row past both
+@pytest.mark.parametrize("n", [1024, 961])               # whole blocks of 16 and 64 rows; one row past both
 def test_lstm_rows_per_block(n):
     wl = W.make_workload("rnn_imdb", n_inputs=n, n_mutants=300)
-    m, words, kills, score = run_gpu(wl)
+    m, words, kills, score = run_gpu(wl)                 # many slots: 64 rows
     kill = unpack_words(words, n)
-    label = m.get_logits(-1).cpu().numpy().argmax(1)
-    for mid in sample_mutants(m, wl):
-        assert np.array_equal(m.get_logits(mid).cpu().numpy().argmax(1) != label, kill[mid]), mid
+    mids = [-1] + sample_mutants(m, wl)
+    small = [m.get_logits(mid).cpu().numpy() for mid in mids]
+    x = device_inputs(wl)
+    m.run_original(x.repeat([16384 // n + 1] + [1] * (x.dim() - 1))[:16384].contiguous())
+    for mid, z in zip(mids, small):
+        big = m.get_logits(mid).cpu().numpy()
+        for i in range(0, 16384, n):
+            assert np.array_equal(big[i:i + n], z[:16384 - i]), (mid, i)
+        if mid >= 0:
+            assert np.array_equal(z.argmax(1) != small[0].argmax(1), kill[mid]), mid
 
 
 @pytest.mark.parametrize("cfg", ["rnn_imdb", "lstm"])      # the wide kernel and the LDS kernel
