@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <functional>
+#include <map>
 
 namespace mure {
 
@@ -135,10 +136,49 @@ ChainT tensor(const Layout& l, int off, int W) {
   return t;
 }
 
-// dry: the cost and the LDS only, no operations.  `slice`: output channels of an expansion convolution computed at a time for
-// the depthwise node after it (0: all).
-bool build_with_slice(const Graph& g, const ChainInfo& f, int a, int b, const std::set<int>& keep, int slice, bool dry, ChainSeg& s) {
+// An operation as far as its time goes: pixels, channels (in, out) of its
+// output tensor, and for a convolution its instance and split.
+struct ChainWork {
+  int kind, px, c, cout;
+  int ks, tn, groups, splits;
+};
+
+// Clocks of an operation of a block of G images, two blocks on the CU: a least
+// squares fit to 860 chains of 2 to 40 operations over some 16,000 images
+// (seeded networks, residual and inverted residual ones; planes of 4 to 32, 8
+// to 512 channels).  The sums are 0.8 to 1.13 of the measured time from the
+// 5th to the 95th percentile.  Per operation what its latency costs, then what
+// its turns of a wave, and its bytes, do.
+double op_clocks(const ChainWork& w, int G) {
+  auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+  const int64_t n = (int64_t)G * w.px;
+  constexpr int NT = CHAIN_WAVES * 64;
+  switch (w.kind) {
+    case CH_LOAD: return 4100 + 0.12 * (double)(n * w.c * 2);
+    case CH_STORE: return 6700 + 0.13 * (double)(n * w.c * 2);
+    case CH_DW: return 1650 + 1430.0 * up(n * w.cout / 16, NT) + 3050.0 / 16 / NT * (double)(n * w.cout);
+    case CH_ADD: return 1900.0 * up(n * w.c / 8, NT);
+    case CH_GAP: return 10600 + 86.0 * w.px * up(G * up(w.c, 64), CHAIN_WAVES);
+    default: break;
+  }
+  if (!w.ks) {                                         // conv32: items of 32 pixels x 32 channels
+    const int64_t items = up(n, 32) * (w.cout / 32);
+    return up(items, CHAIN_WAVES) * (5400 + 49.0 * w.c) + 7.5 * w.c * (double)std::min<int64_t>(items, CHAIN_WAVES);
+  }
+  const int tp = w.tn * w.ks <= 6 ? 2 : 1;             // conv16: w.c its whole reduction
+  const int64_t it = up(up(up(n, 16), tp), w.splits) * up(w.groups, CHAIN_WAVES);
+  // weights past the 64 KB that the operation before touches into the cache
+  const double cold = std::max(0.0, 2.0 * w.cout * w.c - 65536);
+  return 450 + 0.15 * w.cout * w.c * w.splits + 0.05 * cold + it * (1120.0 + 180 * tp * w.tn);
+}
+
+// `slice`: output channels of an expansion convolution computed at a time for
+// the depthwise node after it (0: all).  work: what the operations do, instead
+// of the operations themselves (nullptr: the operations).
+bool build_with_slice(const Graph& g, const ChainInfo& f, int a, int b, const std::set<int>& keep, int slice,
+                      std::vector<ChainWork>* work, ChainSeg& s) {
   s = ChainSeg();
+  if (work) work->clear();
   s.a = a;
   const int N = b + 1;
   std::vector<int> last(N, -1);                       // last reader in [a, b]
@@ -163,7 +203,13 @@ bool build_with_slice(const Graph& g, const ChainInfo& f, int a, int b, const st
   int nops = 0;
   auto push = [&](const ChainOp& o) {
     ++nops;
-    if (!dry) s.ops.push_back(o);
+    if (!work) {
+      s.ops.push_back(o);
+      return;
+    }
+    const bool c16 = o.kind == CH_CONV && o.code > 1;
+    const int px = o.kind == CH_GAP ? o.H * o.W : o.Ho * o.Wo;
+    work->push_back({o.kind, px, c16 ? o.K : o.C, o.Cout, c16 ? o.code % 1000 / 10 : 0, c16 ? o.code % 10 : 0, o.groups, o.splits});
   };
   Arena ar;
   std::vector<Layout> lay(N);
@@ -179,7 +225,6 @@ bool build_with_slice(const Graph& g, const ChainInfo& f, int a, int b, const st
     o.in = o.out = tensor(lay[t], off[t], n.W);
     o.zero = kind == CH_LOAD && lay[t].bd;
     push(o);
-    s.cost += (double)n.out_elems() * 2 / 9;
   };
   auto release_dead = [&](int v) {                    // tensors no node after v reads
     for (int t = 0; t < N; ++t)
@@ -205,20 +250,18 @@ bool build_with_slice(const Graph& g, const ChainInfo& f, int a, int b, const st
     o.lw = ilog2(n.W); o.lp = ilog2(n.H * n.W);
     o.n0 = n0;
     o.node = v;
+    o.w = f.rank[v];
     o.wbytes = cout * o.K * 2;
     o.woff = n0 * o.K * 2;
     if (halo) {
       o.code = 1;                                     // 0: swizzled input
-      s.cost += (double)n.c_out * n.fan_in * 2 * 4 / 48;
     } else {
       const int ks = ks_of(n), tn = tn_of(n, cout);
       o.code = (n.kh == 3 ? 1000 : 0) + ks * 10 + tn;
       o.groups = (cout + 16 * tn - 1) / (16 * tn);
       o.splits = std::max(1, CHAIN_WAVES / o.groups);
       o.inv = 255 / o.groups + 1;
-      s.cost += (double)cout * n.fan_in * 2 * o.splits / 48;
     }
-    s.cost += 2000;
     return o;
   };
   auto dw_op = [&](int v, int n0, int c) {
@@ -229,17 +272,15 @@ bool build_with_slice(const Graph& g, const ChainInfo& f, int a, int b, const st
     o.stride = n.stride; o.relu = n.relu; o.lw = ilog2(n.W); o.lp = ilog2(n.H * n.W);
     o.n0 = n0; o.oc = n0;
     o.node = v;
+    o.w = f.rank[v];
     o.wbytes = c * 18;
     o.woff = n0 * 18;
     o.dcv = make_divu32((uint32_t)(c / 4));
-    s.cost += 2000;
     return o;
   };
-  double per_block = 0;                               // cost shared by a block's images
   for (int v = a; v <= b; ++v) {
     const Node& n = g.nodes[v];
     if (!f.ok[v] || ar.peak + CHAIN_EXTRA > CHAIN_LDS || nops > CHAIN_OPS) return false;
-    const double before = s.cost;
     if (n.kind == K_GAP) {
       if (off[n.in[0]] < 0) return false;
       ChainOp o;
@@ -249,8 +290,6 @@ bool build_with_slice(const Graph& g, const ChainInfo& f, int a, int b, const st
       o.buf = buf_of(v);
       if (o.buf < 0) return false;
       push(o);
-      s.cost += 400;
-      per_block += 400;
       release_dead(v);
       continue;
     }
@@ -282,7 +321,6 @@ bool build_with_slice(const Graph& g, const ChainInfo& f, int a, int b, const st
         push(q);
       }
       ar.release(eo);
-      per_block += s.cost - before;
       if (stored(w)) io(CH_STORE, w);
       release_dead(w);
       v = w;
@@ -317,9 +355,7 @@ bool build_with_slice(const Graph& g, const ChainInfo& f, int a, int b, const st
       o.cpad = (n.C - sn.C) / 2;
       o.dcv = make_divu32((uint32_t)(n.C / 8));
       o.skip = tensor(lay[n.in[1]], off[n.in[1]], sn.W);
-      s.cost += 600;
     }
-    per_block += s.cost - before;
     if (off[n.in[0]] < 0) return false;
     o.in = tensor(lay[n.in[0]], off[n.in[0]], n.inW);
     if (o.kind == CH_CONV && f.fam[v] == FAM_HALO && o.in.mask) o.code = 0;
@@ -351,7 +387,6 @@ bool build_with_slice(const Graph& g, const ChainInfo& f, int a, int b, const st
   s.arena = (ar.peak + 127) / 128 * 128;
   if (s.arena + CHAIN_EXTRA > CHAIN_LDS || nops > CHAIN_OPS) return false;
   s.gmax = std::min(8, (CHAIN_LDS - CHAIN_EXTRA) / s.arena);
-  s.cost += per_block * (1.0 / s.gmax - 1.0);
   s.b = b;
   return true;
 }
@@ -359,30 +394,85 @@ bool build_with_slice(const Graph& g, const ChainInfo& f, int a, int b, const st
 }  // namespace
 
 namespace {
-// The cheapest way to slice the expansions of a .. b (-1: it does not fit).
-double cheapest(const Graph& g, const ChainInfo& f, int a, int b, const std::set<int>& keep, int& slice) {
+// Whole runs of 125 networks layer by layer against their chains, by the size
+// of the run (256, 1,024, 4,096, and 16,384 and 65,536 rows): what a launch less
+// saves (nothing where launches queue up behind each other), and a chain's
+// operations against its layers, both by the estimates here -- few rows leave
+// a block its CU alone; in large runs layers wait for the activations that the
+// ones before them still write.  Measured 0.73, 0.92, 0.94 and 0.9; a little
+// more here, where a last turn of blocks is often nearly empty and against the
+// estimates' error.
+constexpr double LAUNCH_US[CHAIN_SIZES] = {6, 6, 3.5, 0.5}, CHAIN_SCALE[CHAIN_SIZES] = {0.75, 1, 1, 0.95};
+// Estimates per image are in clocks of one of 256 CUs.
+double launch_clocks(int size) { return LAUNCH_US[size] * 256 * 2400 / CHAIN_ROWS[size]; }
+constexpr double ADD_READ = 0.09;                      // a byte of the shortcut, in a convolution's launch
+
+// Estimated clocks per image of a chain of these operations in runs of each size.
+void chain_clocks(const std::vector<ChainWork>& work, int gmax, double (&clocks)[CHAIN_SIZES]) {
+  int last = 0;
+  double t = 0;
+  for (int z = 0; z < CHAIN_SIZES; ++z) {
+    const int G = chain_images(gmax, CHAIN_ROWS[z], 1);
+    if (G != last) {
+      t = 0;
+      for (const ChainWork& w : work) t += op_clocks(w, G);
+      last = G;
+    }
+    clocks[z] = CHAIN_SCALE[z] * t / (2 * G) + launch_clocks(z);
+  }
+}
+
+// The cheapest way to slice the expansions of a .. b for runs of each size:
+// clocks per image and the slice.  false: it does not fit.
+bool cheapest(const Graph& g, const ChainInfo& f, int a, int b, const std::set<int>& keep, std::vector<ChainWork>& work,
+              double (&best)[CHAIN_SIZES], int (&slice)[CHAIN_SIZES]) {
   bool expands = false;
   for (int v = a; v < b; ++v) expands = expands || (g.nodes[v + 1].kind == K_DWCONV && g.nodes[v].kind == K_CONV);
-  double best = -1;
   int fits = 0;
   for (int sl : {0, 96, 48, 32, 16}) {
     ChainSeg t;
     if ((sl && !expands) || fits == 2) break;          // two that fit: finer ones only add operations
-    if (!build_with_slice(g, f, a, b, keep, sl, true, t)) continue;
+    if (!build_with_slice(g, f, a, b, keep, sl, &work, t)) continue;
+    double c[CHAIN_SIZES];
+    chain_clocks(work, t.gmax, c);
+    for (int z = 0; z < CHAIN_SIZES; ++z) {
+      if (fits && c[z] >= best[z]) continue;
+      best[z] = c[z];
+      slice[z] = sl;
+    }
     ++fits;
-    if (best >= 0 && t.cost >= best) continue;
-    best = t.cost;
-    slice = sl;
   }
-  return best;
+  return fits > 0;
+}
+
+// Estimated clocks per image of node v as a launch of its own: its bytes, and
+// for a convolution the work of its tiles; a fit to 2,400 layers of the same
+// networks, 0.8 to 1.15 of the measured time.
+double layer_clocks(const Graph& g, const ChainInfo& f, int v, int size) {
+  const Node& n = g.nodes[v];
+  auto up = [](int64_t a, int64_t b) { return (double)((a + b - 1) / b * b); };
+  const double in = 2.0 * n.inH * n.inW * n.inC, out = 2.0 * n.out_elems(), px = (double)n.Hc * n.Wc;
+  const double t = launch_clocks(size);
+  if (n.kind == K_ADD) return t + 0.22 * out;
+  if (n.kind == K_GAP) return t + 0.1 * in + 1.25 * n.inH * n.inW;
+  if (n.kind == K_CONV) {
+    const double macs = px * n.c_out * n.fan_in;
+    if (f.fam[v] == FAM_HALO) return t + 0.113 * in + 0.19 * out + 0.0005 * macs;
+    if (f.fam[v] == FAM_VALU) return t + 0.052 * in + 0.424 * out + 0.008 * macs;
+    return t + 0.077 * in + 0.06 * out + px * (0.247 * up(n.c_out, 16) + 0.0008 * up(n.c_out, 64) * up(n.fan_in, 32));
+  }
+  return t + 0.09 * in + 0.2 * out;
 }
 }  // namespace
 
 ChainInfo::ChainInfo(const Graph& g) {
   const int n = (int)g.nodes.size();
   fam.resize(n); fused.resize(n); readers.assign(n, 0); last.assign(n, -1); ok.resize(n); convs.resize(n);
-  for (int v = 0; v < n; ++v) {
+  rank.resize(n);
+  for (int v = 0, r = 0; v < n; ++v) {
     const Node& nd = g.nodes[v];
+    rank[v] = r;
+    r += nd.weighted();
     fam[v] = node_family(g, v);
     fused[v] = fused_add_of(g, v);
     ok[v] = chainable(g, v);
@@ -394,43 +484,91 @@ ChainInfo::ChainInfo(const Graph& g) {
   }
 }
 
-bool build_chain(const Graph& g, const ChainInfo& f, int a, int b, const std::set<int>& keep, ChainSeg& s) {
-  int slice = 0;
-  return cheapest(g, f, a, b, keep, slice) >= 0 && build_with_slice(g, f, a, b, keep, slice, false, s);
+bool build_chain(const Graph& g, const ChainInfo& f, int a, int b, const std::set<int>& keep, int size, ChainSeg& s) {
+  int slice[CHAIN_SIZES];
+  double clocks[CHAIN_SIZES];
+  std::vector<ChainWork> work;
+  if (!cheapest(g, f, a, b, keep, work, clocks, slice) || !build_with_slice(g, f, a, b, keep, slice[size], nullptr, s))
+    return false;
+  s.cost = clocks[size];
+  return true;
 }
 bool build_chain(const Graph& g, int a, int b, const std::set<int>& keep, ChainSeg& s) {
-  return build_chain(g, ChainInfo(g), a, b, keep, s);
+  return build_chain(g, ChainInfo(g), a, b, keep, 0, s);
 }
 
-std::vector<ChainSeg> plan_chains(const Graph& g) { return plan_chains(g, ChainInfo(g)); }
-std::vector<ChainSeg> plan_chains(const Graph& g, const ChainInfo& f) {
+double layers_clocks(const Graph& g, const ChainInfo& f, int a, int b, const std::set<int>& keep, int size) {
+  double t = 0;
+  for (int v = a; v <= b; ++v) {
+    t += layer_clocks(g, f, v, size);
+    if (f.fused[v] != v + 1 || v == b || keep.count(v)) continue;
+    ++v;                                               // the ADD in its launch
+    t += ADD_READ * 2 * g.nodes[v].out_elems();
+  }
+  return t;
+}
+
+std::vector<ChainSeg> plan_chains(const Graph& g) { return plan_chains(g, ChainInfo(g)).best[0]; }
+ChainPlan plan_chains(const Graph& g, const ChainInfo& f) {
+  constexpr int S = CHAIN_SIZES;
   const int n = (int)g.nodes.size();
-  std::vector<ChainSeg> best(n);
-  if (g.dtype != DT_BF16) return best;
-  std::vector<double> cost(n + 1, 0);
-  std::vector<int> end(n, 0), sliced(n, 0);
+  ChainPlan plan;
+  for (auto& l : plan.best) l.resize(n);
+  for (auto& l : plan.head) l.resize(n);
+  if (g.dtype != DT_BF16) return plan;
+  struct Best { double cost = 0, chain = 0; int end = 0, slice = 0; };
+  std::vector<Best> at[S], head[S];
+  std::vector<ChainWork> work;
+  for (auto& l : at) l.resize(n + 1);
+  for (auto& l : head) l.resize(n + 1);
   for (int v = n - 1; v >= 1; --v) {
-    const Node& nd = g.nodes[v];
-    cost[v] = cost[v + 1] + ((double)nd.out_elems() + (double)nd.inH * nd.inW * nd.inC) * 2 / 9 + 1000;
+    // by itself, or with the ADD that its launch computes
+    const int fa = f.fused[v];
+    for (int z = 0; z < S; ++z)
+      at[z][v].cost = layer_clocks(g, f, v, z) + (fa == v + 1 ? ADD_READ * 2 * g.nodes[fa].out_elems() + at[z][v + 2].cost
+                                                            : at[z][v + 1].cost);
+    // the copy of node v - 1's output that the layers need (a halo convolution
+    // reads it in channel groups instead); a chain that reads through channel
+    // maps saved its launch and 0.08 clocks a byte of the same networks' time
+    const Node& m = g.nodes[v - 1];
+    const bool copied = m.weighted() && f.fam[v] != FAM_HALO;
+    for (int z = 0; z < S; ++z) {
+      head[z][v] = at[z][v];
+      if (copied) head[z][v].cost += launch_clocks(z) + 0.08 * 2 * m.out_elems();
+    }
     int fails = 0;
     for (int b = v; b < n && f.ok[b] && fails < 2; ++b) {
       // two nodes at least, and not between a convolution and the ADD that its
       // launch would fuse
       if (b == v || f.fused[b] == b + 1) continue;
-      int slice = 0;
-      const double c = cheapest(g, f, v, b, {}, slice);
-      if (c < 0) { ++fails; continue; }
+      int slice[S];
+      double clocks[S];
+      if (!cheapest(g, f, v, b, {}, work, clocks, slice)) { ++fails; continue; }
       fails = 0;
-      if (c + cost[b + 1] < cost[v]) {
-        cost[v] = c + cost[b + 1];
-        end[v] = b;
-        sliced[v] = slice;
+      for (int z = 0; z < S; ++z) {
+        const Best c = {clocks[z] + at[z][b + 1].cost, clocks[z], b, slice[z]};
+        if (c.cost < at[z][v].cost) at[z][v] = c;
+        if (c.cost < head[z][v].cost && f.last[v - 1] <= b) head[z][v] = c;
       }
     }
   }
-  for (int v = 1; v < n; ++v)
-    if (end[v] && !build_with_slice(g, f, v, end[v], {}, sliced[v], false, best[v])) best[v] = ChainSeg();
-  return best;
+  std::map<std::pair<int, int>, ChainSeg> built;       // of the node: by end and slice
+  auto build = [&](int v, const Best& c, ChainSeg& s) {
+    if (!c.end) return;
+    const auto k = built.emplace(std::make_pair(c.end, c.slice), ChainSeg());
+    ChainSeg& b = k.first->second;
+    if (k.second && !build_with_slice(g, f, v, c.end, {}, c.slice, nullptr, b)) b = ChainSeg();
+    s = b;
+    s.cost = c.chain;
+  };
+  for (int v = 1; v < n; ++v) {
+    built.clear();
+    for (int z = 0; z < S; ++z) {
+      build(v, at[z][v], plan.best[z][v]);
+      if (g.nodes[v - 1].weighted()) build(v, head[z][v].end ? head[z][v] : at[z][v], plan.head[z][v]);
+    }
+  }
+  return plan;
 }
 
 }  // namespace mure

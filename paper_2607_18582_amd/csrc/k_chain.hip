@@ -622,7 +622,9 @@ __global__ __launch_bounds__(NT, 4) void chain_kernel(ChainArgs a) {
   uint64_t* const ptrs = reinterpret_cast<uint64_t*>(k.sm + k.zero + 32);
   if (k.tid < 2 * a.nops) {
     const ChainOp* const op = a.ops + (k.tid >> 1);
-    ptrs[k.tid] = op->wbytes > 0 ? reinterpret_cast<const uint64_t*>(a.tabs)[(k.tid & 1 ? op->b : op->w) + k.slot] : 0;
+    ptrs[k.tid] = 0;
+    if (op->wbytes > 0)
+      ptrs[k.tid] = reinterpret_cast<const uint64_t*>(a.tabs)[a.tab0 + (2 * op->w + (k.tid & 1)) * a.tab_stride + k.slot];
   }
   __syncthreads();
   for (int i = 0; i < a.nops; ++i) {

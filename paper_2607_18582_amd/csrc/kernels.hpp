@@ -315,7 +315,7 @@ struct ChainOp {
   int zero = 0;                          // out has a border to clear
   int groups = 1, splits = 1, inv = 256; // conv16: groups of channel tiles, parts of the pixel
                                          // tiles, and (w inv) >> 8 = w / groups for w < CHAIN_WAVES
-  int node = 0, w = 0, b = 0;            // weighted ops: node, offsets into the pointer tables
+  int node = 0, w = 0;                   // weighted ops: node, its rank among the weighted nodes
   int wbytes = 0, woff = 0;              // ... bytes of its weights (0: none) and where they start
   int buf = 0;                           // LOAD, STORE, GAP: launch buffer
   DivU32 dcv;                            // divider by C / 8 (DW: by C / 4; CONV: unused)
@@ -331,7 +331,10 @@ constexpr int CHAIN_BUFS = 24;
 struct ChainArgs {
   const ChainOp* ops = nullptr;          // device
   int nops = 0;
-  const void* const* tabs = nullptr;     // pointer tables, offset to the launch's first slot
+  // pointer tables: the weights (bias: + 1) of the node of rank w for slot s are
+  // tabs[tab0 + (2 w + 0) tab_stride + s]
+  const void* const* tabs = nullptr;
+  int64_t tab0 = 0, tab_stride = 0;
   int nslots = 0, nx = 0, x0 = 0;
   int G = 1, arena = 0;                  // images per block, LDS bytes per image
   int per_slot = 0, turns = 0, end = 0;  // filled by the launcher: blocks per slot; blocks per XCD

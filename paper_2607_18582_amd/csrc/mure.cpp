@@ -104,9 +104,16 @@ struct mure_ctx {
   int32_t* slotv = nullptr;
   int32_t* chmapv = nullptr;
   DeltaCol* colv = nullptr;
-  ChainOp* chainv = nullptr;
   std::unique_ptr<Chains> chains;                     // of the loaded model
-  Run orig_run;                                       // run_original's launches (cached nodes stored)
+  DevBuf d_chain;                                     // their operations
+  // run_original's launches by the size of the run: those that store the cached
+  // nodes `kept`, and the operations of the chains that this takes
+  struct OrigRun {
+    bool planned = false;
+    std::set<int> kept;
+    Run run;
+    DevBuf ops;
+  } orig_run[CHAIN_SIZES];
   struct GroupTabs {
     std::map<int, int64_t> w, b;                      // node -> offset (in pointers) into tables
     int64_t slot_mutant = 0;                          // offset (int32) into slotv
@@ -121,8 +128,7 @@ struct mure_ctx {
     int64_t vgent = 0;                                // vhalo: offset (int32) into chmapv of the
                                                       // (slot, group) entries, one per side plane
     std::vector<int64_t> vgbeg;                       // vhalo: first entry of each slot (+1)
-    Run run;                                          // the suffix's launches (ops: in chainv)
-    bool vchain = false;                              // the first chain reads mmi's output through
+    bool vchain[CHAIN_SIZES] = {};                    // the first chain reads mmi's output through
                                                       // channel maps and is its only reader
   };
   std::vector<GroupTabs> gtabs;
@@ -424,11 +430,11 @@ mure_status exec_node(mure_ctx* ctx, int v, const std::vector<Where>& ins, void*
 // Whether the first chain of group gr's suffix can read mmi's output from the
 // prefix cache, the mutants' channel maps and compact delta rows: it starts
 // right after mmi and is its only reader.
-bool chain_reads_mmi(const std::vector<ChainSeg>& chains, const Graph& g, const Group& gr) {
+bool chain_reads_mmi(const Chains& chains, int size, const Graph& g, const Group& gr) {
   if (gr.mmi >= g.out() || !(gr.delta || gr.n_recompute == 0)) return false;
-  const ChainSeg& s = chains[gr.mmi + 1];
-  if (!s.valid() || s.ins.empty() || s.ins[0] != gr.mmi) return false;
-  for (int v = s.b + 1; v <= g.out(); ++v)
+  const ChainSeg* const s = chains.head[size][gr.mmi + 1].get();
+  if (!s || s->ins.empty() || s->ins[0] != gr.mmi) return false;
+  for (int v = s->b + 1; v <= g.out(); ++v)
     for (int k = 0; k < g.nodes[v].n_in; ++k)
       if (g.nodes[v].in[k] == gr.mmi) return false;
   return true;
@@ -437,20 +443,22 @@ bool chain_reads_mmi(const std::vector<ChainSeg>& chains, const Graph& g, const 
 // Launch a chain over slots [0, nslots) of a chunk of nx inputs from x0 on;
 // `where` gives the buffers of its inputs and stored outputs, vin (optional)
 // the view of its first input.
+// ops: the device table that its operations are in; tab0, tab_stride: the
+// pointer tables' entry of the first weighted node and the first slot, and the
+// slots of a table.
 template <typename F>
-mure_status exec_chain(mure_ctx* ctx, const RunChain& c, F&& where, const VirtualIn* vin,
-                       int cs0, int nslots, int nx, int x0, bool timed) {
+mure_status exec_chain(mure_ctx* ctx, const RunChain& c, const DevBuf& ops, F&& where, const VirtualIn* vin,
+                       int64_t tab0, int64_t tab_stride, int nslots, int nx, int x0, bool timed) {
   const Graph& g = ctx->g;
-  const ChainSeg& s = c.seg;
+  const ChainSeg& s = *c.seg;
   ChainArgs a;
-  a.ops = ctx->chainv + c.ops;
+  a.ops = ops.as<const ChainOp>() + s.at;
   a.nops = (int)s.ops.size();
-  a.tabs = ctx->tables + cs0;
+  a.tabs = ctx->tables;
+  a.tab0 = tab0; a.tab_stride = tab_stride;
   a.nslots = nslots; a.nx = nx; a.x0 = x0;
   a.arena = s.arena;
-  // fewer images per block while the launch would leave the chip idle
-  a.G = s.gmax;
-  while (a.G > 1 && (int64_t)((nx + a.G - 1) / a.G) * nslots < 1024) --a.G;
+  a.G = chain_images(s.gmax, nx, nslots);
   if (vin) a.vin = *vin;
   int nb = 0;
   double bytes = 0;
@@ -615,6 +623,7 @@ static mure_status load_model_impl(mure_ctx* ctx, const mure_layer* layers, int3
     if (need && (!hw || !hb)) return ctx->fail(MURE_E_INVALID, "node " + std::to_string(i) + ": weights and bias required");
     if (!need && (hw || hb)) return ctx->fail(MURE_E_INVALID, "node " + std::to_string(i) + ": has no parameters");
   }
+  auto chains = std::make_unique<Chains>(g);
   if (!ctx->plan_only) {
     HIPTRY(hipSetDevice(ctx->device));
     // from here on a device failure leaves the context without a model
@@ -662,10 +671,16 @@ static mure_status load_model_impl(mure_ctx* ctx, const mure_layer* layers, int3
       }
       HIPTRY(hipMemcpyAsync(ctx->d_b[i]->p, biases[i], bb, hipMemcpyHostToDevice, ctx->stream));
     }
+    if (!chains->ops.empty()) {
+      HIPTRY(ctx->d_chain.ensure(chains->ops.size() * sizeof(ChainOp)));
+      HIPTRY(hipMemcpyAsync(ctx->d_chain.p, chains->ops.data(), chains->ops.size() * sizeof(ChainOp),
+                            hipMemcpyHostToDevice, ctx->stream));
+    }
     HIPTRY(hipStreamSynchronize(ctx->stream));
   }
   ctx->g = std::move(g);
-  ctx->chains.reset(new Chains(ctx->g));
+  ctx->chains = std::move(chains);
+  for (auto& o : ctx->orig_run) o.planned = false;
   ctx->have_graph = true;
   ctx->plan = Plan();
   ctx->recs.clear();
@@ -830,25 +845,15 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
       ow[v] = (int64_t)tabs.size(); tabs.push_back(ctx->d_w[v]->p);
       ob[v] = (int64_t)tabs.size(); tabs.push_back(ctx->d_b[v]->p);
     }
-    std::vector<ChainOp> chops;
-    // the chains' operations with their pointer-table offsets
-    auto add_chains = [&](Run& run, const std::map<int, int64_t>& w, const std::map<int, int64_t>& b) {
-      for (RunChain& c : run.chains) {
-        c.ops = (int64_t)chops.size();
-        for (ChainOp o : c.seg.ops) {
-          if (o.wbytes > 0) {
-            o.w = (int)w.at(o.node);
-            o.b = (int)b.at(o.node);
-          }
-          chops.push_back(o);
-        }
-      }
-    };
     for (size_t gi = 0; gi < plan.groups.size(); ++gi) {
       Group& gr = plan.groups[gi];
       mure_ctx::GroupTabs& gt = gtabs[gi];
-      gt.vchain = chain_reads_mmi(ctx->chains->best, g, gr);
-      if (gt.vchain) virtual_map(g, plan, gr);
+      bool vchain = false;
+      for (int z = 0; z < CHAIN_SIZES; ++z) {
+        gt.vchain[z] = chain_reads_mmi(*ctx->chains, z, g, gr);
+        vchain = vchain || gt.vchain[z];
+      }
+      if (vchain) virtual_map(g, plan, gr);
       for (int v = gr.mmi; v < (int)g.nodes.size(); ++v) {
         if (!g.nodes[v].weighted()) continue;
         gt.w[v] = (int64_t)tabs.size();
@@ -862,12 +867,6 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
           tabs.push_back(it == cow_index.end() ? ctx->d_b[v]->p : (const void*)cargs[it->second].b_dst);
         }
       }
-      // mmi's output is not materialised for readers through maps or groups
-      gt.run = plan_run(g, gr.mmi + 1, ctx->chains.get(), true, {}, [&](const ChainSeg& seg) {
-        const bool reads = std::find(seg.ins.begin(), seg.ins.end(), gr.mmi) != seg.ins.end();
-        return !(reads && (gr.virt || gr.vhalo) && !gt.vchain);
-      });
-      add_chains(gt.run, gt.w, gt.b);
       gt.slot_mutant = (int64_t)slots.size();
       for (int mu : gr.mutants) slots.push_back(mu);
       gt.chmap = (int64_t)chmaps.size();
@@ -901,8 +900,6 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
         chmaps.insert(chmaps.end(), ent.begin(), ent.end());
       }
     }
-    Run orun = plan_run(g, 1, ctx->chains.get(), true, std::set<int>(plan.cache_nodes.begin(), plan.cache_nodes.end()));
-    add_chains(orun, ow, ob);
     // touched-channel lists of the recompute mutants (CSR, absolute offsets
     // into the list stored after every group's offsets)
     {
@@ -951,7 +948,6 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
     const size_t o_cols = section(cols.size() * sizeof(DeltaCol));
     const size_t o_cargs = section(cargs.size() * sizeof(CowArgs));
     const size_t o_drecs = section(drecs.size() * sizeof(DevRecord));
-    const size_t o_chops = section(chops.size() * sizeof(ChainOp));
     const size_t o_noise = section((size_t)pool_n * 4);
     HIPTRY(ctx->h_apply.ensure(std::max<size_t>(total, 256)));
     HIPTRY(ctx->d_apply.ensure(std::max<size_t>(total, 256)));
@@ -965,7 +961,6 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
     put(o_cols, cols.data(), cols.size() * sizeof(DeltaCol));
     put(o_cargs, cargs.data(), cargs.size() * sizeof(CowArgs));
     put(o_drecs, drecs.data(), drecs.size() * sizeof(DevRecord));
-    put(o_chops, chops.data(), chops.size() * sizeof(ChainOp));
     fill_pool(reinterpret_cast<float*>(h + o_noise), segs, pool_n);
     hipStream_t st = ctx->stream;
     char* d = ctx->d_apply.as<char>();
@@ -974,7 +969,6 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
     ctx->slotv = reinterpret_cast<int32_t*>(d + o_slots);
     ctx->chmapv = reinterpret_cast<int32_t*>(d + o_chmap);
     ctx->colv = reinterpret_cast<DeltaCol*>(d + o_cols);
-    ctx->chainv = reinterpret_cast<ChainOp*>(d + o_chops);
     int64_t cow_max = 0, fan_max = 0;
     for (const CowArgs& a : cargs) {
       cow_max = std::max(cow_max, (int64_t)a.c_out * a.fan_in * es);
@@ -990,7 +984,6 @@ static mure_status apply_mutants_impl(mure_ctx* ctx, int32_t n_mutants, const mu
     (void)hipEventElapsedTime(&ms, ctx->ev0, ctx->ev1);
     ctx->stats.ms_apply = ms;
     ctx->gtabs = std::move(gtabs);
-    ctx->orig_run = std::move(orun);
     ctx->orig_w = std::move(ow);
     ctx->orig_b = std::move(ob);
   }
@@ -1055,8 +1048,25 @@ static mure_status run_original_impl(mure_ctx* ctx, const void* inputs_dev, int6
   }
   std::set<int> external(cached);
   external.insert(L);
-  const Run layers = ctx->fused ? Run() : plan_run(g, 1, nullptr, false, cached);
-  const Run& run = ctx->fused ? ctx->orig_run : layers;
+  mure_ctx::OrigRun layers;
+  mure_ctx::OrigRun& orig = ctx->fused ? ctx->orig_run[chain_size(n)] : layers;
+  if (!ctx->fused) {
+    orig.run = plan_run(g, 1, nullptr, 0, false, false, cached);
+  } else if (!orig.planned || orig.kept != cached) {
+    orig.planned = false;
+    orig.run = plan_run(g, 1, ctx->chains.get(), chain_size(n), false, true, cached);
+    orig.kept = cached;
+    std::vector<ChainOp> ops;
+    for (const RunChain& c : orig.run.chains)
+      if (c.own) ops.insert(ops.end(), c.seg->ops.begin(), c.seg->ops.end());
+    if (!ops.empty()) {
+      HIPTRY(orig.ops.ensure(ops.size() * sizeof(ChainOp)));
+      HIPTRY(hipMemcpyAsync(orig.ops.p, ops.data(), ops.size() * sizeof(ChainOp), hipMemcpyHostToDevice, ctx->stream));
+      HIPTRY(hipStreamSynchronize(ctx->stream));
+    }
+    orig.planned = true;
+  }
+  const Run& run = orig.run;
   const Placement pl = place_buffers(g, run, external);
   const int64_t budget = ctx->max_ws_mb << 20;
   int64_t nx = n;
@@ -1084,7 +1094,8 @@ static mure_status run_original_impl(mure_ctx* ctx, const void* inputs_dev, int6
     };
     for (const RunStep& step : run.steps) {
       if (step.chain >= 0) {
-        mure_status st = exec_chain(ctx, run.chains[step.chain], where, nullptr, 0, 1, cnt, (int)x0, false);
+        const RunChain& c = run.chains[step.chain];
+        mure_status st = exec_chain(ctx, c, c.own ? orig.ops : ctx->d_chain, where, nullptr, 0, 1, 1, cnt, (int)x0, false);
         if (st != MURE_OK) return st;
         continue;
       }
@@ -1141,7 +1152,8 @@ static mure_status run_original_impl(mure_ctx* ctx, const void* inputs_dev, int6
 }  // extern "C"
 namespace {
 struct ChunkGeom {
-  Run layers;                                        // the launches without chains
+  Run run;                                           // the launches
+  bool vchain = false;                               // mmi's output read by a chain, through maps
   Placement pl;
   int64_t nx = 0, spc = 0, cap_rows = 0, need_bytes = 0;
 };
@@ -1149,11 +1161,22 @@ struct ChunkGeom {
 // chains: with the cluster's chains (whose inner nodes take no buffers).
 ChunkGeom group_geometry(const mure_ctx* ctx, int gi, int nslots, int64_t budget, bool chains) {
   const Graph& g = ctx->g;
-  const int mmi = ctx->plan.groups[gi].mmi;
+  const Group& gr = ctx->plan.groups[gi];
+  const int mmi = gr.mmi;
   const int64_t N = ctx->N;
   ChunkGeom cg;
-  if (!chains) cg.layers = plan_run(g, mmi + 1, nullptr, ctx->fused != 0, {});
-  cg.pl = place_buffers(g, chains ? ctx->gtabs[gi].run : cg.layers, {}, mmi);
+  if (chains) {
+    const int size = chain_size(nslots * N);
+    cg.vchain = ctx->gtabs[gi].vchain[size];
+    // mmi's output is not materialised for readers through maps or groups
+    cg.run = plan_run(g, mmi + 1, ctx->chains.get(), size, true, true, {}, [&](const ChainSeg& s) {
+      const bool reads = std::find(s.ins.begin(), s.ins.end(), mmi) != s.ins.end();
+      return !(reads && (gr.virt || gr.vhalo) && !cg.vchain);
+    });
+  } else {
+    cg.run = plan_run(g, mmi + 1, nullptr, 0, false, ctx->fused != 0, {});
+  }
+  cg.pl = place_buffers(g, cg.run, {}, mmi);
   const int64_t peak = std::max<int64_t>(cg.pl.peak, 1);
   int64_t nx = N;
   if (ctx->chunk_inputs) nx = std::min<int64_t>(nx, ctx->chunk_inputs);
@@ -1191,14 +1214,14 @@ static mure_status run_group(mure_ctx* ctx, int gi, int s_begin, int s_end, uint
     chains = false;
     cg = group_geometry(ctx, gi, s_end - s_begin, budget, false);
   }
-  const Run& run = chains ? gt.run : cg.layers;
+  const Run& run = cg.run;
   const Placement& pl = cg.pl;
   const int64_t nx = cg.nx, spc = cg.spc, cap_rows = cg.cap_rows;
   // channel-group reads of mmi's output by its halo consumers (not with a
   // caller's scratch array: the side planes live in a buffer of their own)
   const Node& nmm = g.nodes[mmi];
   const int64_t vP = (int64_t)nmm.H * nmm.W;
-  const bool vc = gt.vchain && chains;             // mmi's output read by a chain, through maps
+  const bool vc = cg.vchain;
   const bool vh = gr.vhalo && !vc && ctx->group_reads && ctx->fused && !ws && nx * vP < INT32_MAX;
   if (vh) {
     int64_t most = 0;
@@ -1216,6 +1239,9 @@ static mure_status run_group(mure_ctx* ctx, int gi, int s_begin, int s_end, uint
     ws = ctx->d_ws.as<char>();
   }
   const void* const* tabs = ctx->tables;
+  // the cluster's tables are those of its weighted nodes from mmi on, in order:
+  // where the first weighted node's would begin
+  const int64_t tab0 = gt.w.at(mmi) - 2 * (int64_t)ctx->chains->info.rank[mmi] * (int64_t)gr.mutants.size();
   const int32_t* slot_mut = ctx->slotv + gt.slot_mutant;
   const Node& nm = g.nodes[mmi];
   const void* mmi_cache = mmi == L ? ctx->d_logits.p : (ctx->cache.count(mmi) ? ctx->cache[mmi]->p : nullptr);
@@ -1338,9 +1364,9 @@ static mure_status run_group(mure_ctx* ctx, int gi, int s_begin, int s_end, uint
         if (step.chain >= 0) {
           const bool first = vc && v == mmi + 1;
           mure_status st = exec_chain(
-              ctx, run.chains[step.chain],
+              ctx, run.chains[step.chain], ctx->d_chain,
               [&](int p) -> Where { return first && p == mmi ? Where{mmi_cache, MODE_CACHE} : where(p); },
-              first ? &vin : nullptr, cs0, ns, cnt, (int)x0, true);
+              first ? &vin : nullptr, tab0 + cs0, (int64_t)gr.mutants.size(), ns, cnt, (int)x0, true);
           if (st != MURE_OK) return st;
           continue;
         }

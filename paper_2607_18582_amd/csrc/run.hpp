@@ -7,6 +7,7 @@
 
 #include <functional>
 #include <map>
+#include <memory>
 #include <set>
 #include <vector>
 
@@ -16,8 +17,8 @@
 namespace mure {
 
 struct RunChain {
-  ChainSeg seg;
-  int64_t ops = 0;                 // its first operation in the device table
+  std::shared_ptr<const ChainSeg> seg;
+  bool own = false;                // built for this run (not one of the model's)
 };
 
 struct RunStep {
@@ -33,18 +34,21 @@ struct Run {
   std::vector<int> writes(const RunStep& s) const;                   // nodes it stores
 };
 
-// A graph's chains by their first node (plan_chains), and what plan_run needs
-// to build one that stores more of its nodes.
+// A graph's chains by the size of the run and their first node (plan_chains),
+// and what plan_run needs to build one that stores more of its nodes.
 struct Chains {
   ChainInfo info;
-  std::vector<ChainSeg> best;
-  explicit Chains(const Graph& g) : info(g), best(plan_chains(g, info)) {}
+  // null: the node runs by itself
+  std::vector<std::shared_ptr<const ChainSeg>> best[CHAIN_SIZES], head[CHAIN_SIZES];
+  std::vector<ChainOp> ops;        // of every chain (ChainSeg::at)
+  explicit Chains(const Graph& g);
 };
 
-// Nodes first .. out as steps.  chains: nullptr: none; a chain is taken where
-// usable, if given, accepts it.  fuse: convolutions compute their ADD.  kept:
-// nodes whose own output must be stored.
-Run plan_run(const Graph& g, int first, const Chains* chains, bool fuse, const std::set<int>& kept,
+// Nodes first .. out as steps.  chains: the model's for runs of `size`
+// (nullptr: none); a chain is taken where usable, if given, accepts it.  head:
+// first - 1 is a first mutated layer.  fuse: convolutions compute their ADD.
+// kept: nodes whose own output must be stored.
+Run plan_run(const Graph& g, int first, const Chains* chains, int size, bool head, bool fuse, const std::set<int>& kept,
              const std::function<bool(const ChainSeg&)>& usable = {});
 
 // Liveness-based placement of per-row activation buffers: offsets in bytes

@@ -2,8 +2,11 @@
 // UndefinedBehaviorSanitizer by tests/test_run_plan.py: over seeded random
 // bf16 graphs whose residual blocks list the shortcut's projection before or
 // after the main branch, a convolution is fused with its ADD only where the
-// shortcut is computed before the convolution; and the thin convolution kernel
-// is chosen where its blocks have enough pixels.
+// shortcut is computed before the convolution; every launch of a run reads what
+// has been computed, stored and not yet overwritten, and every chain is the one
+// that the graph alone gives; the blocks of a chain's launches are each taken
+// once; and chains, and the thin convolution kernel, are chosen where they are
+// the faster ones.
 #include <algorithm>
 #include <cstdint>
 #include <cstdio>
@@ -108,16 +111,28 @@ void bad(int id, int first, int step, int node, const char* what) {
 // The steps in order.  mmi >= 0: stored before the first step (unless virt:
 // the first chain reads it elsewhere); nodes before `first` are cached;
 // `external` nodes have buffers of their own.
-void walk(const Graph& g, const Run& run, int first, int mmi, bool virt, const std::set<int>& external,
-          const std::set<int>& kept, int id) {
+void walk(const Graph& g, const Chains& model, int size, const Run& run, int first, int mmi, bool virt,
+          const std::set<int>& external, const std::set<int>& kept, int id) {
   ++runs;
   chains += (int64_t)run.chains.size();
-  for (const RunChain& c : run.chains) {                // as planned from the graph alone
+  int64_t at = 0;
+  for (const RunChain& c : run.chains) {                // as planned from the graph alone, in its table
+    const ChainSeg& t = *c.seg;
     ChainSeg s;
-    if (!build_chain(g, c.seg.a, c.seg.b, kept, s) || s.ops.size() != c.seg.ops.size() || s.ins != c.seg.ins ||
-        s.outs != c.seg.outs || s.arena != c.seg.arena || s.gmax != c.seg.gmax ||
-        memcmp(s.ops.data(), c.seg.ops.data(), s.ops.size() * sizeof(ChainOp)))
-      bad(id, first, 0, c.seg.a, "starts another chain than build_chain's");
+    if (!build_chain(g, model.info, t.a, t.b, kept, size, s) || s.ops.size() != t.ops.size() || s.ins != t.ins ||
+        s.outs != t.outs || s.arena != t.arena || s.gmax != t.gmax ||
+        memcmp(s.ops.data(), t.ops.data(), s.ops.size() * sizeof(ChainOp)))
+      bad(id, first, 0, t.a, "starts another chain than build_chain's");
+    if (c.own ? t.at != at : t.at + t.ops.size() > model.ops.size() ||
+                             memcmp(&model.ops[t.at], t.ops.data(), t.ops.size() * sizeof(ChainOp)))
+      bad(id, first, 0, t.a, "starts a chain whose operations are elsewhere");
+    if (c.own) at += (int64_t)t.ops.size();
+    for (const ChainOp& o : t.ops)                       // two table entries per weighted node before it
+      if (o.wbytes > 0) {
+        int rank = 0;
+        for (int v = 0; v < o.node; ++v) rank += g.nodes[v].weighted();
+        if (o.w != rank) bad(id, first, 0, o.node, "has another rank");
+      }
   }
   const Placement pl = place_buffers(g, run, external, mmi);
   std::vector<int> owner(pl.peak / 256, -1);            // buffers are whole units of 256 bytes
@@ -148,7 +163,7 @@ void walk(const Graph& g, const Run& run, int first, int mmi, bool virt, const s
     const RunStep& s = run.steps[i];
     std::set<int> done;
     if (s.chain >= 0) {
-      const ChainSeg& c = run.chains[s.chain].seg;
+      const ChainSeg& c = *run.chains[s.chain].seg;
       for (int v = c.a; v <= c.b; ++v) done.insert(v);
     } else {
       done.insert(s.v);
@@ -193,36 +208,42 @@ void check(const Build& b, int id, Rng& r) {
     if (g.nodes[fa].in[1] >= v) bad(id, 0, 0, v, "adds a node computed after it");
   }
   const Chains chains(g);
-  const std::vector<ChainSeg>& best = chains.best;
-  for (int mmi = 1; mmi < L; ++mmi) {
-    if (!g.nodes[mmi].weighted()) continue;
-    // mmi's output stored; read by the first chain only; and not by a chain
-    walk(g, plan_run(g, mmi + 1, &chains, true, {}), mmi + 1, mmi, false, {}, {}, id);
-    bool only = best[mmi + 1].valid();
-    for (int v = best[mmi + 1].b + 1; v <= L && only; ++v)
-      for (int k = 0; k < g.nodes[v].n_in; ++k) only = only && g.nodes[v].in[k] != mmi;
-    if (only) walk(g, plan_run(g, mmi + 1, &chains, true, {}), mmi + 1, mmi, true, {}, {}, id);
-    const Run apart = plan_run(g, mmi + 1, &chains, true, {}, [&](const ChainSeg& s) {
-      for (int p : s.ins)
-        if (p == mmi) return false;
-      return true;
-    });
-    walk(g, apart, mmi + 1, mmi, false, {}, {}, id);
-    for (const RunStep& s : apart.steps)                // group reads rely on it
-      if (s.chain < 0 && s.add < 0 && g.nodes[s.v].kind == K_ADD && g.nodes[s.v].in[1] == mmi &&
-          g.nodes[s.v].in[0] > mmi && fused_add_of(g, g.nodes[s.v].in[0]) == s.v)
-        bad(id, mmi + 1, 0, s.v, "reads mmi as a shortcut and is not fused");
-    walk(g, plan_run(g, mmi + 1, nullptr, true, {}), mmi + 1, mmi, false, {}, {}, id);
-    walk(g, plan_run(g, mmi + 1, nullptr, false, {}), mmi + 1, mmi, false, {}, {}, id);
-  }
-  for (int t = 0; t < 6; ++t) {                         // the original's run
-    std::set<int> kept, ext;
-    for (int v = 1; v < L; ++v)
-      if (t && r.below(t > 3 ? 8 : 2) == 0) kept.insert(v);
-    ext = kept;
-    ext.insert(L);
-    walk(g, plan_run(g, 1, t % 2 ? &chains : nullptr, t < 4, kept), 1, -1, false, ext, kept, id);
-    walk(g, plan_run(g, 1, &chains, true, kept), 1, -1, false, ext, kept, id);
+  for (int size = 0; size < CHAIN_SIZES; ++size) {
+    auto go = [&](const Run& run, int first, int mmi, bool virt, const std::set<int>& ext, const std::set<int>& kept) {
+      walk(g, chains, size, run, first, mmi, virt, ext, kept, id);
+    };
+    for (int mmi = 1; mmi < L; ++mmi) {
+      if (!g.nodes[mmi].weighted()) continue;
+      // mmi's output stored; read by the first chain only; and not by a chain
+      const Run run = plan_run(g, mmi + 1, &chains, size, true, true, {});
+      go(run, mmi + 1, mmi, false, {}, {});
+      const ChainSeg* const head = chains.head[size][mmi + 1].get();
+      bool only = head != nullptr;
+      for (int v = only ? head->b + 1 : L + 1; v <= L && only; ++v)
+        for (int k = 0; k < g.nodes[v].n_in; ++k) only = only && g.nodes[v].in[k] != mmi;
+      if (only) go(run, mmi + 1, mmi, true, {}, {});
+      const Run apart = plan_run(g, mmi + 1, &chains, size, true, true, {}, [&](const ChainSeg& s) {
+        for (int p : s.ins)
+          if (p == mmi) return false;
+        return true;
+      });
+      go(apart, mmi + 1, mmi, false, {}, {});
+      for (const RunStep& s : apart.steps)              // group reads rely on it
+        if (s.chain < 0 && s.add < 0 && g.nodes[s.v].kind == K_ADD && g.nodes[s.v].in[1] == mmi &&
+            g.nodes[s.v].in[0] > mmi && fused_add_of(g, g.nodes[s.v].in[0]) == s.v)
+          bad(id, mmi + 1, 0, s.v, "reads mmi as a shortcut and is not fused");
+      go(plan_run(g, mmi + 1, nullptr, 0, false, true, {}), mmi + 1, mmi, false, {}, {});
+      go(plan_run(g, mmi + 1, nullptr, 0, false, false, {}), mmi + 1, mmi, false, {}, {});
+    }
+    for (int t = 0; t < 6; ++t) {                       // the original's run
+      std::set<int> kept, ext;
+      for (int v = 1; v < L; ++v)
+        if (t && r.below(t > 3 ? 8 : 2) == 0) kept.insert(v);
+      ext = kept;
+      ext.insert(L);
+      go(plan_run(g, 1, t % 2 ? &chains : nullptr, size, false, t < 4, kept), 1, -1, false, ext, kept);
+      go(plan_run(g, 1, &chains, size, false, true, kept), 1, -1, false, ext, kept);
+    }
   }
 }
 
@@ -267,6 +288,29 @@ void check_thin() {
       ++failures;
     }
 }
+// Large runs take chains where they were measured faster than their layers:
+// (plane, channels, filter, layers, with a chain), the last before a GAP.
+// Layers' time over the chain's: 2.1 for three 3x3 layers of 16 at 32 x 32; 0.3 for a
+// 1x1 layer and its GAP there, 0.9 for 1x1 layers of 384 at 4 x 4.
+void check_choice() {
+  const int t[][5] = {{32, 16, 3, 8, 1}, {32, 16, 1, 1, 0}, {4, 384, 1, 4, 0}};
+  for (const auto& c : t) {
+    Build b(c[0], 3);
+    int x = b.conv(0, c[1], 3, 1, 1);
+    for (int i = 0; i < c[3]; ++i) x = b.conv(x, c[1], c[2], 1, 1);
+    b.head(x);
+    Graph g;
+    g.nodes = b.g;
+    if (!build_graph(g, b.h, b.h, b.c, DT_BF16).empty()) { ++failures; continue; }
+    const Chains chains(g);
+    const Run run = plan_run(g, 2, &chains, CHAIN_SIZES - 1, false, true, {});
+    if (run.chains.empty() != (c[4] == 0)) {
+      printf("%d x %d, %d channels, %d x %d: wrong launches\n", c[0], c[0], c[1], c[2], c[2]);
+      ++failures;
+    }
+  }
+}
+
 // a chain's blocks over launches of CHAIN_GRID: each block once
 void check_grid() {
   for (const int64_t blocks : {(int64_t)1, (int64_t)7, (int64_t)4097, (int64_t)CHAIN_GRID, (int64_t)CHAIN_GRID + 5}) {
@@ -288,6 +332,7 @@ int main(int argc, char** argv) {
   Rng r{77};
   check_thin();
   check_grid();
+  check_choice();
   name = "mobilenet";
   check(mobilenet(6, {32, 16, 24, 32, 64, 96, 160, 320, 1280}), 0, r);
   check(mobilenet(6, {16, 8, 16, 16, 32, 48, 80, 160, 640}), 1, r);

@@ -1,8 +1,8 @@
 """What a run launches and where its tensors stand (csrc/run.cpp with
 csrc/chain.cpp and csrc/plan.cpp) built for the host with AddressSanitizer and
 UndefinedBehaviorSanitizer (tests/native/run_check.cpp): every launch reads
-tensors that are computed, stored and not yet overwritten, and the thin
-convolution kernel runs where it is the faster one."""
+tensors that are computed, stored and not yet overwritten, and chains and the
+thin convolution kernel run where they are the faster ones."""
 import os
 import shutil
 import subprocess
