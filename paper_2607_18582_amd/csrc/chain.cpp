@@ -17,18 +17,19 @@ int ilog2(int v) {
 bool pow2(int v) { return v > 0 && (v & (v - 1)) == 0; }
 bool plane_ok(int H, int W) { return pow2(H) && pow2(W) && H >= 4 && W >= 4 && W <= 32 && H <= 32; }
 
-// k steps of 32 that the conv16 instances exist for
-constexpr int KS1[] = {1, 2, 3, 5, 9, 12};       // 1 x 1 filters
-constexpr int KS3[] = {5, 9};                    // 3 x 3 filters
+// Most k steps of 32 of a conv16 instance, of the fewest that hold the node's
+// reduction (0: none does): a wave keeps their weights in registers, and the
+// offsets of the taps beside them (3 x 3: up to 32 channels).
+constexpr int STEPS1[] = {1, 2, 3, 5, 9, 12}, STEPS3[] = {5, 9};
 
 int ks_of(const Node& n) {
-  const int need = (int)((n.fan_in + 31) / 32);
+  const int64_t need = (n.fan_in + 31) / 32;
   if (n.kh == 1) {
-    for (int k : KS1)
-      if (k == need) return k;
+    for (int k : STEPS1)
+      if (need <= k) return k;
   } else {
-    for (int k : KS3)
-      if (k == need) return k;
+    for (int k : STEPS3)
+      if (need <= k) return k;
   }
   return 0;
 }
@@ -257,6 +258,7 @@ bool build_with_slice(const Graph& g, const ChainInfo& f, int a, int b, const st
       o.code = 1;                                     // 0: swizzled input
     } else {
       const int ks = ks_of(n), tn = tn_of(n, cout);
+      s.past = s.past || n.fan_in <= 32 * (ks - 1);
       o.code = (n.kh == 3 ? 1000 : 0) + ks * 10 + tn;
       o.groups = (cout + 16 * tn - 1) / (16 * tn);
       o.splits = std::max(1, CHAIN_WAVES / o.groups);

@@ -21,6 +21,7 @@ struct ChainSeg {
                                    // buffer i of the launch is ins[i], then outs
   int arena = 0;                   // LDS bytes per image
   int gmax = 0;                    // most images per block
+  bool past = false;               // some convolution leaves steps of its instance empty
   double cost = 0;                 // planner's estimate, clocks per image
   int64_t at = 0;                  // its first operation in its table of operations
   bool valid() const { return b >= a; }

@@ -162,11 +162,18 @@ struct Epi {
   }
 };
 
-// Convolution in the tiled implicit GEMM's order: KS k-steps of 32 (in the
-// last one k past K has zero weights and reads the zero slot), TN channel
-// tiles of 16 per wave, K3: 3 x 3 taps (pad 1), else 1 x 1.  The input is not
-// swizzled, so a fragment's address is the pixel's plus the step's part.
-template <int KS, int TN, bool K3, int R, int AR>
+// Convolution in the tiled implicit GEMM's order: KS k-steps of 32 (k past K
+// has zero weights and reads the zero slot), TN channel tiles of 16 per wave,
+// K3: 3 x 3 taps (pad 1), else 1 x 1.  The input is not swizzled, so a
+// fragment's address is the pixel's plus the step's part.  PAST: some of the
+// steps may be empty.
+//
+// Instances for 1, 2, 3, 5, 9 and 12 steps serve every reduction up to 12; one
+// for each number of steps made every chain slower, whatever it runs (the
+// kernel 290 -> 390 KB; MobileNetV2, 2,500 x 200: 46.0 -> 49.0 ms with 1 x 1 instances
+// only, 54 with the 3 x 3 ones), and so, by 2 %, do the empty steps' conditions:
+// chains without any run a kernel without them.
+template <int KS, int TN, bool K3, int R, int AR, bool PAST>
 __device__ __forceinline__ void conv16(const Blk& k, cop* o, const bf16_t* Wt, const float* bias) {
   constexpr int TP = TN * KS <= 6 ? 2 : 1;               // pixel tiles in flight
   const int l15 = k.lane & 15, g4 = k.lane >> 4;
@@ -178,15 +185,20 @@ __device__ __forceinline__ void conv16(const Blk& k, cop* o, const bf16_t* Wt, c
   const int ptiles = (k.G << lp) >> 4;
   const PxMap im(it, 1 << lw);
   const int istride = it.pxb * o->stride;
-  const bool tail = 32 * (KS - 1) + 8 * g4 >= K;
+  // k past K: in the last step, or with PAST from the instance's least number
+  // of steps on
+  constexpr int LAST = !PAST || KS <= 3 ? KS - 1 : KS == 5 ? 2 : KS == 9 ? 5 : 9;
+  auto past = [&](int s) { return s >= LAST && 32 * s + 8 * g4 >= K; };
   int toff[K3 ? KS : 1];
   if constexpr (K3) {
-    // 16 or 32 channels; pad 1: the border shifts a pixel to its first tap
-    const int lc = KS == 5 ? 4 : 5;
+    // vector u of 8 k is channels 8 (u % c8) .. of tap u / c8, c8 = C / 8: 2 or
+    // 4 where the steps are full, 1 to 4 otherwise ((u inv) >> 8 is exact for
+    // u < 48); pad 1: the border shifts a pixel to its first tap
+    const int c8 = PAST ? o->C >> 3 : KS == 5 ? 2 : 4, inv = PAST ? 255 / c8 + 1 : 256 / c8;
 #pragma unroll
     for (int s = 0; s < KS; ++s) {
-      const int kk = 32 * s + 8 * g4, t = kk >> lc, dy = (t * 11) >> 5;
-      toff[s] = __umul24(__umul24(dy, it.pitch) + t - 3 * dy, it.pxb) + 2 * (kk & ((1 << lc) - 1)) + it.off;
+      const int u = 4 * s + g4, t = (u * inv) >> 8, dy = (t * 11) >> 5;
+      toff[s] = __umul24(__umul24(dy, it.pitch) + t - 3 * dy, it.pxb) + 16 * (u - t * c8) + it.off;
     }
   } else {
     toff[0] = im.bd1 * it.pxb + it.off + 16 * g4;
@@ -204,7 +216,7 @@ __device__ __forceinline__ void conv16(const Blk& k, cop* o, const bf16_t* Wt, c
 #pragma unroll
       for (int s = 0; s < KS; ++s) {
         v4u r = {0u, 0u, 0u, 0u};
-        if (n < Cout && (s + 1 < KS || !tail)) r = *(gv4u*)(Wt + (n0 + n) * K + 32 * s + 8 * g4);
+        if (n < Cout && !past(s)) r = *(gv4u*)(Wt + (n0 + n) * K + 32 * s + 8 * g4);
         w[j][s] = __builtin_bit_cast(v8bf, r);
       }
       const int c = (cg * TN + j) * 16 + 4 * g4;
@@ -228,7 +240,7 @@ __device__ __forceinline__ void conv16(const Blk& k, cop* o, const bf16_t* Wt, c
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
           const unsigned char* ad = K3 ? base + toff[K3 ? s : 0] : base + toff[0] + 64 * s;
-          if (s + 1 == KS && tail) ad = k.sm + k.zero;
+          if (past(s)) ad = k.sm + k.zero;
           f[i][s] = *reinterpret_cast<const v8bf*>(ad);
         }
       }
@@ -429,7 +441,7 @@ __device__ __forceinline__ void dw(const Blk& k, cop* o, const bf16_t* Wt, const
   }
 }
 
-template <int R, int AR>
+template <int R, int AR, bool PAST>
 __device__ __forceinline__ void conv(const Blk& k, cop* o, const bf16_t* Wt, const float* bias) {
   switch (o->code) {
     // two pixel tiles per wave where that leaves every wave some
@@ -438,7 +450,7 @@ __device__ __forceinline__ void conv(const Blk& k, cop* o, const bf16_t* Wt, con
       else conv32<1, true, R, AR>(k, o, Wt, bias);
       break;
     case 1: conv32<1, false, R, AR>(k, o, Wt, bias); break;
-#define MURE_C16(KS, TN, K3) case (K3 ? 1000 : 0) + KS * 10 + TN: conv16<KS, TN, K3, R, AR>(k, o, Wt, bias); break;
+#define MURE_C16(KS, TN, K3) case (K3 ? 1000 : 0) + KS * 10 + TN: conv16<KS, TN, K3, R, AR, PAST>(k, o, Wt, bias); break;
     MURE_C16(1, 1, false) MURE_C16(1, 2, false) MURE_C16(1, 3, false)
     MURE_C16(2, 1, false) MURE_C16(2, 2, false) MURE_C16(2, 3, false)
     MURE_C16(3, 1, false) MURE_C16(3, 2, false)
@@ -600,6 +612,13 @@ __device__ __forceinline__ void gap_rows(const Blk& k, const ChainOp& o, const C
 }
 }  // namespace
 
+__device__ __forceinline__ ChainOp fetch_op(cop* o) {
+  ChainOp c;
+  __builtin_memcpy(&c, (const void __attribute__((address_space(4)))*)o, sizeof(c));
+  return c;
+}
+
+template <bool PAST>
 __global__ __launch_bounds__(NT, 4) void chain_kernel(ChainArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char chain_sm[];
   // the blocks running together on an XCD share their slot's weights in its L2
@@ -646,12 +665,12 @@ __global__ __launch_bounds__(NT, 4) void chain_kernel(ChainArgs a) {
       // the epilogue's forms: activation or none, or a plain convolution with
       // its ADD
       if (o->add) {
-        if (o->add_relu) conv<0, 1>(k, o, Wt, bias);
-        else conv<0, 0>(k, o, Wt, bias);
+        if (o->add_relu) conv<0, 1, PAST>(k, o, Wt, bias);
+        else conv<0, 0, PAST>(k, o, Wt, bias);
       } else if (o->relu) {
-        conv<1, -1>(k, o, Wt, bias);
+        conv<1, -1, PAST>(k, o, Wt, bias);
       } else {
-        conv<0, -1>(k, o, Wt, bias);
+        conv<0, -1, PAST>(k, o, Wt, bias);
       }
     } else if (kind == CH_DW) {
       if (o->stride == 1) {
@@ -663,8 +682,7 @@ __global__ __launch_bounds__(NT, 4) void chain_kernel(ChainArgs a) {
       }
     } else {
       begin(k, o);
-      ChainOp c;
-      __builtin_memcpy(&c, (const void __attribute__((address_space(4)))*)o, sizeof(c));
+      const ChainOp c = fetch_op(o);
       if (kind == CH_LOAD) load_rows(k, c, a, a.buf[c.buf], reinterpret_cast<int32_t*>(ptrs + 2 * CHAIN_OPS));
       else if (kind == CH_STORE) store_rows(k, c, a, a.buf[c.buf]);
       else if (kind == CH_ADD) add_rows(k, c);
@@ -687,7 +705,10 @@ hipError_t launch_chain(const ChainArgs& a0, hipStream_t s) {
     a.first = (int)b0;
     a.end = (int)std::min<int64_t>(b0 + CHAIN_GRID, blocks);
     a.turns = (a.end - a.first + 7) / 8;
-    hipLaunchKernelGGL(chain_kernel, dim3((unsigned)(a.turns * 8)), dim3(NT), (size_t)(a.G * a.arena + CHAIN_EXTRA), s, a);
+    const dim3 grid((unsigned)(a.turns * 8));
+    const size_t lds = (size_t)(a.G * a.arena + CHAIN_EXTRA);
+    if (a.past) hipLaunchKernelGGL(chain_kernel<true>, grid, dim3(NT), lds, s, a);
+    else hipLaunchKernelGGL(chain_kernel<false>, grid, dim3(NT), lds, s, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -337,6 +337,7 @@ struct ChainArgs {
   int64_t tab0 = 0, tab_stride = 0;
   int nslots = 0, nx = 0, x0 = 0;
   int G = 1, arena = 0;                  // images per block, LDS bytes per image
+  int past = 0;                          // some convolution leaves steps of its instance empty
   int per_slot = 0, turns = 0, end = 0;  // filled by the launcher: blocks per slot; blocks per XCD
   int first = 0;                         // of this launch, its first block and one past its last
   VirtualIn vin;                         // buffer 0 read through channel maps (vin.chmap set)

@@ -458,6 +458,7 @@ mure_status exec_chain(mure_ctx* ctx, const RunChain& c, const DevBuf& ops, F&& 
   a.tab0 = tab0; a.tab_stride = tab_stride;
   a.nslots = nslots; a.nx = nx; a.x0 = x0;
   a.arena = s.arena;
+  a.past = s.past;
   a.G = chain_images(s.gmax, nx, nslots);
   if (vin) a.vin = *vin;
   int nb = 0;
