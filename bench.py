@@ -38,14 +38,16 @@ PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}    # MI355X dense MFMA
 KERNELS = ["dense_kernel (DENSE layers, MFMA GEMM)",
            "conv_valu_kernel (CONV2D with few output channels, vector ALU)",
            "conv_lds_kernel (CONV2D, LDS-resident images, MFMA)",
-           "conv_mfma_kernel (CONV2D, im2col implicit GEMM with scalar gathers, MFMA)",
+           "conv_mfma_kernel (CONV2D, im2col implicit GEMM with scalar gathers, MFMA; conv_thin_kernel for bf16 stems)",
            "conv_big_kernel (bf16 CONV2D, tiled implicit GEMM, MFMA)",
            "dw_col_kernel (depthwise CONV2D, vector ALU; dw_full_kernel for filters other than 3x3)",
            "embed_kernel (token embedding gather)",
            "lstm_kernel (LSTM recursion, MFMA per step)",
-           "conv_halo_kernel (bf16 3x3 CONV2D, A operand from LDS halo tiles, MFMA)"]
+           "conv_halo_kernel (bf16 3x3 CONV2D, A operand from LDS halo tiles, MFMA)",
+           "chain_kernel (consecutive small bf16 nodes, activations in LDS, MFMA)"]
 KERNEL_NAMES = ["dense_kernel", "conv_valu_kernel", "conv_lds_kernel", "conv_mfma_kernel",
-                "conv_big_kernel", "dw_col_kernel", "embed_kernel", "lstm_kernel", "conv_halo_kernel"]
+                "conv_big_kernel", "dw_col_kernel", "embed_kernel", "lstm_kernel", "conv_halo_kernel",
+                "chain_kernel"]
 VALU_FAMILIES = (1, 5)                           # fused multiply-add chains on the vector ALU
 PEAK_VALU_TFLOPS = 78.6                          # fp32 FMA without packed-fp32 instructions
 PEAK_HBM_GBS = 8000.0
@@ -134,6 +136,7 @@ def read_counters(kernel: str, config: str, n_inputs: int, n_mutants: int):
 
 # kernels of one family (the library times a family's launches together)
 FAMILY_KERNELS = {"lstm_kernel": ("lstm_kernel", "lstm_wide_kernel"),
+                  "conv_mfma_kernel": ("conv_mfma_kernel", "conv_thin_kernel"),
                   "dw_col_kernel": ("dw_col_kernel", "dw_full_kernel", "dw_list_kernel")}
 
 
@@ -412,15 +415,18 @@ def main():
     st = stats[-1]
     peak = PEAK_TFLOPS[md.dtype]
     kernel_peak = lambda f: PEAK_VALU_TFLOPS if f in VALU_FAMILIES else peak
-    kernel_ms = np.mean([s["kernel_ms"] for s in stats], axis=0)
+    kernel_ms = np.mean([s["kernel_ms"] + [s["chain_ms"]] for s in stats], axis=0)
+    kernel_launches = st["kernel_launches"] + [st["chain_launches"]]
+    kernel_macs = st["kernel_macs_algorithmic"] + [st["chain_macs_algorithmic"]]
+    kernel_bytes = st["kernel_bytes_algorithmic"] + [st["chain_bytes_algorithmic"]]
 
     def family_roof(f):
         """Roofline of kernel family f over run_mutants: HBM-bound when its
         algorithmic FLOP per byte sits below the ridge point of its compute
         peak, else bound by that peak."""
         ms = float(kernel_ms[f])
-        flops = 2.0 * st["kernel_macs_algorithmic"][f]
-        nbytes = float(st["kernel_bytes_algorithmic"][f])
+        flops = 2.0 * kernel_macs[f]
+        nbytes = float(kernel_bytes[f])
         intensity = flops / nbytes if nbytes > 0 else float("inf")
         ridge = kernel_peak(f) * 1e12 / (PEAK_HBM_GBS * 1e9)
         if intensity < ridge:
@@ -436,7 +442,7 @@ def main():
     # the dominant kernel of run_mutants (largest summed launch time)
     fam = int(np.argmax(kernel_ms))
     roof, ms_k, alg_flops, alg_bytes, intensity, ridge = family_roof(fam)
-    launches = st["kernel_launches"][fam]
+    launches = kernel_launches[fam]
     ms_gemm = float(np.mean([s["ms_gemm"] for s in stats]))
     all_flops = 2.0 * st["gemm_macs_algorithmic"]
     all_achieved = all_flops / (ms_gemm * 1e-3) / 1e12 if ms_gemm > 0 else 0.0
@@ -445,10 +451,10 @@ def main():
     # every kernel family that ran: time, launches and its own roofline
     families = {}
     for f in range(len(KERNEL_NAMES)):
-        if st["kernel_launches"][f] > 0:
+        if kernel_launches[f] > 0:
             r = family_roof(f)[0]
             families[KERNEL_NAMES[f]] = {"ms": round(float(kernel_ms[f]), 4),
-                                         "launches": int(st["kernel_launches"][f]),
+                                         "launches": int(kernel_launches[f]),
                                          "bound": r["bound"], "frac": round(r["frac"], 4)}
     line = {
         "metric": "mutant-input suffix evals/sec + MFMA/HBM roofline fraction, 1 MI355X",

@@ -175,9 +175,11 @@ typedef struct {
   int64_t gemm_macs_algorithmic, gemm_macs_executed;
   /* The same, split by kernel (MURE_N_KERNELS entries): [0] dense GEMM,
    * [1] vector-ALU convolution (few output channels), [2] LDS-resident
-   * convolution, [3] im2col implicit GEMM with scalar gathers, [4] tiled bf16
-   * implicit GEMM, [5] depthwise convolution, [6] embedding lookup, [7] LSTM
-   * recursion, [8] bf16 3x3 convolution over LDS halo tiles. */
+   * convolution, [3] implicit GEMM with scalar gathers (of the bf16 stems: from
+   * LDS), [4] tiled bf16 implicit GEMM, [5] depthwise convolution, [6] embedding
+   * lookup, [7] LSTM recursion, [8] bf16 3x3 convolution over LDS halo tiles.
+   * Chains of consecutive small bf16 nodes in one launch are in gemm_* and
+   * ms_gemm, and by themselves in mure_chain_stats. */
   int64_t kernel_launches[MURE_N_KERNELS];
   double kernel_ms[MURE_N_KERNELS];
   int64_t kernel_macs_algorithmic[MURE_N_KERNELS];
@@ -298,6 +300,17 @@ mure_status mure_mutant_plan(const mure_ctx* ctx, int32_t mutant_id, int32_t* mm
 
 /* Work/timing counters of the most recent calls (host output). */
 mure_status mure_get_stats(const mure_ctx* ctx, mure_stats* out);
+
+/* The chains of the last run_mutants (option "kernel_timing" = 1; zeros
+ * otherwise): launches that compute consecutive small bf16 nodes with the
+ * activations between them on chip.  Bytes: a chain's inputs, outputs and weights. */
+typedef struct {
+  int64_t launches;
+  double ms;
+  int64_t macs_algorithmic;
+  double bytes_algorithmic;
+} mure_chain_stats;
+mure_status mure_get_chain_stats(const mure_ctx* ctx, mure_chain_stats* out);
 
 /* Tuning and testing knobs (name, integer value).  Known names:
  *   "max_workspace_mb"  cap on per-chunk activation buffers (default 65536)

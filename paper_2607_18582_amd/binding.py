@@ -31,7 +31,7 @@ INPUT, DENSE, CONV2D, ADD, GAP, FLATTEN, DWCONV, EMBED, LSTM = 0, 1, 2, 3, 4, 5,
 EXPORTED = ["mure_version", "mure_create", "mure_load_model", "mure_apply_mutants",
             "mure_run_original", "mure_run_mutants", "mure_run_mutants_noalloc",
             "mure_get_logits", "mure_mutant_plan",
-            "mure_get_stats", "mure_set_option", "mure_last_error", "mure_destroy"]
+            "mure_get_stats", "mure_get_chain_stats", "mure_set_option", "mure_last_error", "mure_destroy"]
 
 
 class mure_layer(C.Structure):
@@ -68,6 +68,11 @@ class mure_stats(C.Structure):
                 ("kernel_bytes_algorithmic", C.c_double * N_KERNELS),
                 ("n_classes", C.c_int64), ("n_inputs", C.c_int64), ("n_mutants", C.c_int64),
                 ("group_planes", C.c_int64), ("ms_mmi", C.c_double)]
+
+
+class mure_chain_stats(C.Structure):
+    _fields_ = [("launches", C.c_int64), ("ms", C.c_double), ("macs_algorithmic", C.c_int64),
+                ("bytes_algorithmic", C.c_double)]
 
 
 def _pack(arrays, R: int, dtype):
@@ -135,6 +140,7 @@ def load_library(path: str = LIB_PATH) -> C.CDLL:
         "mure_mutant_plan": (C.c_int, [P, C.c_int32, C.POINTER(C.c_int32), C.POINTER(C.c_int32),
                                        C.POINTER(C.c_int32), C.c_int32, C.POINTER(C.c_int32)]),
         "mure_get_stats": (C.c_int, [P, C.POINTER(mure_stats)]),
+        "mure_get_chain_stats": (C.c_int, [P, C.POINTER(mure_chain_stats)]),
         "mure_set_option": (C.c_int, [P, C.c_char_p, C.c_int64]),
         "mure_last_error": (C.c_char_p, [P]),
         "mure_destroy": (None, [P]),
@@ -322,6 +328,9 @@ class Mure:
         for k, _ in mure_stats._fields_:
             v = getattr(s, k)
             out[k] = list(v) if isinstance(v, C.Array) else v
+        c = mure_chain_stats()
+        self._check(self.lib.mure_get_chain_stats(self.ctx, C.byref(c)))
+        out.update(("chain_" + k, getattr(c, k)) for k, _ in mure_chain_stats._fields_)
         return out
 
     def set_option(self, name: str, value: int):

@@ -158,6 +158,7 @@ struct mure_ctx {
   std::vector<char> tevent_mmi;                       // ... and whether it computed a first mutated node
   size_t tevents_used = 0;
   mure_stats stats{};
+  mure_chain_stats chain_stats{};
 
   mure_status fail(mure_status s, const std::string& m) {
     err = m;
@@ -486,25 +487,22 @@ mure_status exec_chain(mure_ctx* ctx, const RunChain& c, const DevBuf& ops, F&& 
     hipError_t ee = hipEventRecord(ctx->tevents[ctx->tevents_used + 1], ctx->stream);
     if (ee != hipSuccess) return ctx->dev_fail(ee, "hipEventRecord");
     ctx->tevents_used += 2;
-    // counted with the family that does most of its multiply-accumulates
-    int64_t macs = 0, by_fam[N_FAMILIES] = {};
+    int64_t macs = 0;
     for (int v = s.a; v <= s.b; ++v) {
       const Node& n = g.nodes[v];
       if (!n.weighted()) continue;
       macs += n.macs;
-      by_fam[node_family(g, v)] += n.macs;
       bytes += (double)nslots * n.n_weights() * es;
     }
-    const int fam = (int)(std::max_element(by_fam, by_fam + N_FAMILIES) - by_fam);
     const int64_t total = macs * nx * nslots;
-    ctx->tevent_family.push_back(fam);
+    ctx->tevent_family.push_back(FAM_CHAIN);
     ctx->tevent_mmi.push_back(0);
     ctx->stats.gemm_launches++;
     ctx->stats.gemm_macs_algorithmic += total;
     ctx->stats.gemm_macs_executed += total;
-    ctx->stats.kernel_launches[fam]++;
-    ctx->stats.kernel_macs_algorithmic[fam] += total;
-    ctx->stats.kernel_bytes_algorithmic[fam] += bytes;
+    ctx->chain_stats.launches++;
+    ctx->chain_stats.macs_algorithmic += total;
+    ctx->chain_stats.bytes_algorithmic += bytes;
   }
   return MURE_OK;
 }
@@ -687,6 +685,7 @@ static mure_status load_model_impl(mure_ctx* ctx, const mure_layer* layers, int3
   ctx->recs.clear();
   reset_cache(ctx);
   ctx->stats = mure_stats{};
+  ctx->chain_stats = mure_chain_stats{};
   ctx->state = 1;
   return MURE_OK;
 }
@@ -1498,6 +1497,7 @@ static mure_status run_mutants_impl(mure_ctx* ctx, uint64_t* kill_bits_dev, int6
     ctx->stats.kernel_macs_algorithmic[f] = 0;
     ctx->stats.kernel_bytes_algorithmic[f] = 0;
   }
+  ctx->chain_stats = mure_chain_stats{};
   ctx->tevents_used = 0;
   ctx->tevent_family.clear();
   ctx->tevent_mmi.clear();
@@ -1531,7 +1531,8 @@ static mure_status run_mutants_impl(mure_ctx* ctx, uint64_t* kill_bits_dev, int6
     float t = 0.f;
     HIPTRY(hipEventElapsedTime(&t, ctx->tevents[i], ctx->tevents[i + 1]));
     ctx->stats.ms_gemm += t;
-    ctx->stats.kernel_ms[ctx->tevent_family[i / 2]] += t;
+    const int fam = ctx->tevent_family[i / 2];
+    (fam == FAM_CHAIN ? ctx->chain_stats.ms : ctx->stats.kernel_ms[fam]) += t;
     if (ctx->tevent_mmi[i / 2]) ctx->stats.ms_mmi += t;
   }
   ctx->tevents_used = 0;
@@ -1704,6 +1705,12 @@ mure_status mure_mutant_plan(const mure_ctx* ctx, int32_t mutant_id, int32_t* mm
 
 mure_status mure_get_stats(const mure_ctx* ctx, mure_stats* out) {
   return guarded(ctx, [&] { return get_stats_impl(ctx, out); });
+}
+
+mure_status mure_get_chain_stats(const mure_ctx* ctx, mure_chain_stats* out) {
+  if (!ctx || !out) return MURE_E_INVALID;
+  *out = ctx->chain_stats;
+  return MURE_OK;
 }
 
 }  // extern "C"

@@ -74,6 +74,7 @@ enum Family {
   FAM_HALO = 8     // bf16 3x3 stride-1 conv, operands from LDS halo and weight tiles per 16-channel chunk
 };
 constexpr int N_FAMILIES = 9;
+constexpr int FAM_CHAIN = N_FAMILIES;   // in the timing of launches only: a chain of small nodes
 // Halo convolution: 512-pixel bands of TR = 512 / W image rows (the bands
 // never straddle two images); a band's halo -- its rows plus the row above
 // and below, per packed image -- holds at most conv_halo_cap(W) pixels, the
