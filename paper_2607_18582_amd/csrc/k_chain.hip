@@ -29,10 +29,10 @@
 // 1024 x 16 convolution alone on a CU, against 2,600 of LDS reads and 1,300 of
 // MFMA) and the vector instructions of the epilogues.
 //
-// Measured, layer by layer -> chains: run_mutants on ResNet-20, exhaustive,
-// 1,111 inputs x 61 mutants 24.2 -> 14.7 ms (10.8 with the stem's own kernel);
-// ResNet-20, 2,500 x 200, 54.8 -> 43 ms (259 -> 133 launches); MobileNetV2,
-// 2,500 x 200, 59.3 -> 42.5 ms (704 -> 194 launches).
+// Measured, layer by layer -> chains where chain.cpp finds them faster:
+// run_mutants on ResNet-20, 2,500 inputs x 200 mutants, 50.6 -> 41.0 ms (237 ->
+// 142 launches); MobileNetV2, 2,500 x 200, 62.7 -> 45.5 ms (705 -> 214); ResNet-20,
+// exhaustive, 1,111 x 61, 24.2 -> 14.7 ms, and 10.4 with the stem's own kernel.
 #include "dev.hpp"
 
 #include <algorithm>
